@@ -234,6 +234,7 @@ dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, i
     g->metric = p.metric;
     g->lp = p.lp;
     for (int a = 0; a < 3; ++a) { g->klo[a] = p.klo[a]; g->size[a] = p.size[a]; }
+    g->zbits = counter_bits == 16 ? 15 : 16;
     g->counter_bits = counter_bits;
     g->row_words = counter_bits == 16 ? (p.size[2] + 1) / 2 : p.size[2];
     const int64_t plane_words = (int64_t)p.size[1] * g->row_words;
@@ -251,6 +252,26 @@ dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, i
     g->slab_words = (int32_t)(pps * plane_words);
     g->wide = 4 * plane_words > 0xFFFF ? 1 : 0;
     return DSES_OK;
+}
+
+// A group's windows cover its own x extent besides the slab's planes, and 64 points
+// span twice the extent of 32 but need half the set-ups and half the loads.  Measured
+// with both (us per rotation, 32 / 64 points): where 64 points span 0.08-0.11 of the
+// slab's planes 1,269 / 1,197 (2,000 x 8,192), 159 / 157 (1,000 x 2,000), 448 / 427
+// (2,000 x 3,000); at 0.14-0.2 of them 78 / 80 (500 x 1,500), 77 / 79 (717 x 1,024),
+// 46 / 48 (300 x 1,000); at 0.4 62 / 68 (1,000 x 500), 265 / 296 (1,500 x 1,500).
+int choose_gref(const Geom &g, bool sorted, float x_extent, int asked)
+{
+    if (!sorted || g.wide) return 0;
+    if (asked) return asked > 32 ? 64 : 32;
+    return 64.0f * x_extent <= 0.13f * (float)g.pps * (float)g.m ? 64 : 32;
+}
+
+StageDesc stage_desc(const Geom &g, int gref, const float *tgt, const int32_t *perm, int32_t *yq,
+                     float *yt)
+{
+    return StageDesc{tgt,     perm, g.m,  g.S16, g.S15, {g.klo[0], g.klo[1], g.klo[2]},
+                     g.zbits, gref ? gref : 64, yq, yt};
 }
 
 // Largest vote count any bin can reach: for a fixed source point the pairs that
@@ -651,7 +672,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
                              &d_scratch)) != DSES_OK)
         return st;
 
-    if ((st = dbuf(c->yq, 4 * m * sizeof(int32_t), &d_yq)) != DSES_OK) return st;
+    if ((st = dbuf(c->yq, stage_words(m) * sizeof(int32_t), &d_yq)) != DSES_OK) return st;
     if ((st = dbuf(c->yt, 3 * m * sizeof(float), &d_yt)) != DSES_OK) return st;
     // with an arena the records go straight to the caller's buffer when it gives one
     if (arena && records)
@@ -673,8 +694,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     a.scratch = sorted ? static_cast<int32_t *>(d_scratch) : nullptr;
     a.scratch_stride = job.n;
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-    a.lane_group = o.lane_group;
-    a.ref_x_extent = ref_x_extent(ylo, yhi);
+    a.gref = choose_gref(g, sorted, ref_x_extent(ylo, yhi), o.lane_group);
 
     if (scorer == DSES_SCORER_GRID) {
         const TargetRes *t = job.target;
@@ -734,8 +754,9 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
                      ref_coord_limit(p), bad};
         DSES_HIP(launch_check(ca, stream));
     }
-    DSES_HIP(launch_stage(job.tgt, static_cast<int32_t *>(d_perm), job.m, g.S16, g.S15, p.klo,
-                          static_cast<int32_t *>(d_yq), static_cast<float *>(d_yt), stream));
+    DSES_HIP(launch_stage(stage_desc(g, a.gref, job.tgt, static_cast<int32_t *>(d_perm),
+                                     static_cast<int32_t *>(d_yq), static_cast<float *>(d_yt)),
+                          stream));
     rec_ev(1);
     if (job.exhaustive) {
         DSES_HIP(launch_exhaustive(a, scorer, grid, stream));

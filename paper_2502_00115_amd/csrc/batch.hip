@@ -64,6 +64,7 @@ struct GraphCache {
     int scorer = -1;
     int cap_count = 0, cap_items = 0, grid = 0;
     hipStream_t stream = nullptr;
+    bool general = false;
 };
 
 struct BatchState {
@@ -144,17 +145,22 @@ static dses_status ensure_capacity(BatchState *b, int count, int n_items, size_t
 }
 
 // Enqueue (or capture) clear -> stage -> sweep -> select -> copy back.
-static dses_status enqueue_batch(BatchState *b, int scorer, int grid, hipStream_t stream)
+static dses_status enqueue_batch(BatchState *b, int scorer, bool general, int grid,
+                                 hipStream_t stream)
 {
     uint32_t *status = static_cast<uint32_t *>(b->status.ptr);
-    uint32_t *cursor = status + b->cap_count;      // one word after the per-instance flags
+    uint32_t *cursor = status + b->cap_count;      // two words after the per-instance flags
     const int32_t *header = static_cast<int32_t *>(b->header.ptr);
-    DSES_HIP(launch_clear(cursor, 1, stream));
+    DSES_HIP(launch_clear(cursor, 2, stream));
     DSES_HIP(launch_batch_aux(static_cast<StageDesc *>(b->stage.ptr), nullptr, header,
                               b->cap_count, 0, stream));
     BatchArgs ba{static_cast<SweepArgs *>(b->inst.ptr), static_cast<BatchItem *>(b->items.ptr),
                  header, cursor, nullptr};
-    DSES_HIP(launch_sweep_batch(ba, scorer, grid, stream));
+    DSES_HIP(launch_sweep_batch(ba, scorer, false, grid, stream));
+    if (general) {
+        ba.cursor = cursor + 1;
+        DSES_HIP(launch_sweep_batch(ba, scorer, true, grid, stream));
+    }
     DSES_HIP(launch_batch_aux(nullptr, static_cast<SelectDesc *>(b->sel.ptr), header,
                               b->cap_count, 1, stream));
     DSES_HIP(hipMemcpyAsync(b->host_res, b->results.ptr, b->cap_count * sizeof(DevResult),
@@ -162,16 +168,16 @@ static dses_status enqueue_batch(BatchState *b, int scorer, int grid, hipStream_
     return DSES_OK;
 }
 
-static dses_status run_graph(BatchState *b, int scorer, int grid, hipStream_t stream)
+static dses_status run_graph(BatchState *b, int scorer, bool general, int grid, hipStream_t stream)
 {
     GraphCache &gc = b->graph[scorer];
     if (!gc.exec || gc.cap_count != b->cap_count || gc.cap_items != b->cap_items ||
-        gc.grid != grid || gc.stream != stream) {
+        gc.grid != grid || gc.stream != stream || gc.general != general) {
         if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
         gc.exec = nullptr;
         hipGraph_t graph = nullptr;
         DSES_HIP(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
-        dses_status st = enqueue_batch(b, scorer, grid, stream);
+        dses_status st = enqueue_batch(b, scorer, general, grid, stream);
         hipError_t e = hipStreamEndCapture(stream, &graph);
         if (st != DSES_OK) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -186,6 +192,7 @@ static dses_status run_graph(BatchState *b, int scorer, int grid, hipStream_t st
         gc.cap_items = b->cap_items;
         gc.grid = grid;
         gc.stream = stream;
+        gc.general = general;
     }
     DSES_HIP(hipGraphLaunch(gc.exec, stream));
     return DSES_OK;
@@ -372,7 +379,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
             if (!T) x.off_tgt = bump(arena_bytes, 3 * (size_t)x.m * sizeof(float));
             if (!q.rotset) x.off_rot = bump(arena_bytes, 9 * (size_t)x.k * sizeof(float));
         }
-        x.off_yq = bump(arena_bytes, 4 * (size_t)x.m * sizeof(int32_t));
+        x.off_yq = bump(arena_bytes, stage_words((size_t)x.m) * sizeof(int32_t));
         x.off_yt = bump(arena_bytes, 3 * (size_t)x.m * sizeof(float));
         x.off_perm = bump(arena_bytes, (size_t)x.m * sizeof(int32_t));
         x.off_rec = bump(arena_bytes, (size_t)x.k * sizeof(dses_record));
@@ -407,9 +414,17 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
             sum_k += x.k;
             ++n_ok;
         }
+    // (the general path's tiles, which a launch of their own runs, at the end of the
+    // list); n_general is their number
+    int n_general = 0;
+    std::vector<int32_t> gref(count, 0);
+    for (int i = 0; i < count; ++i)
+        if (P[i].status == DSES_OK)
+            gref[i] = choose_batch_gref(P[i].g, P[i].sorted, ref_x_extent(P[i].ylo, P[i].yhi));
     auto build_items = [&](int items_per_cu, std::vector<BatchItem> *list) {
         const double target_cost = std::max(1.0, total / ((double)grid * items_per_cu));
-        struct Tile { double cost; BatchItem it; };
+        struct Tile { bool general; double cost; BatchItem it; };
+        n_general = 0;
         std::vector<Tile> tiles;
         for (int i = 0; i < count; ++i) {
             const Prepared &x = P[i];
@@ -420,11 +435,14 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                                  : (int)std::max(1.0, std::min((double)x.k, target_cost / per_rot));
             for (int32_t k0 = 0; k0 < x.k; k0 += tile) {
                 const int32_t k1 = std::min<int32_t>(x.k, k0 + tile);
-                tiles.push_back({per_rot * (k1 - k0), BatchItem{i, k0, k1, 0}});
+                tiles.push_back({gref[i] == 0, per_rot * (k1 - k0), BatchItem{i, k0, k1, 0}});
+                n_general += gref[i] == 0;
             }
         }
         std::stable_sort(tiles.begin(), tiles.end(),
-                         [](const Tile &a, const Tile &bb) { return a.cost > bb.cost; });
+                         [](const Tile &a, const Tile &bb) {
+                             return a.general != bb.general ? bb.general : a.cost > bb.cost;
+                         });
         list->resize(tiles.size());
         for (size_t t = 0; t < tiles.size(); ++t) (*list)[t] = tiles[t].it;
     };
@@ -471,7 +489,8 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         StageDesc &sd = stage[i];
         SelectDesc &sl = sel[i];
         if (x.status != DSES_OK) {       // empty stage/select entries
-            sd = StageDesc{nullptr, nullptr, 0, 1.0, 1.0, {0, 0, 0}, nullptr, nullptr};
+            sd = StageDesc{};
+            sd.gref = 64;
             sl = SelectDesc{nullptr, 0, 1.0f, nullptr, res_dev + i, nullptr};
             continue;
         }
@@ -502,7 +521,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         a.scratch = x.sorted ? static_cast<int32_t *>(b->scratch.ptr) : nullptr;
         a.scratch_stride = max_n;
         source_buckets(x.ylo, x.yhi, x.g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-        a.ref_x_extent = ref_x_extent(x.ylo, x.yhi);
+        a.gref = gref[i];
         a.g = x.g;
         a.rec = reinterpret_cast<dses_record *>(arena + x.off_rec);
         a.k = x.k;
@@ -534,12 +553,10 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                 a.field.inv[q] = x.target->df_inv[q];
             }
         }
-        sd = StageDesc{x.tgt, perm_dev, x.m, x.g.S16, x.g.S15,
-                       {x.p.klo[0], x.p.klo[1], x.p.klo[2]}, const_cast<int32_t *>(a.yq),
-                       const_cast<float *>(a.yt)};
+        sd = stage_desc(x.g, a.gref, x.tgt, perm_dev, const_cast<int32_t *>(a.yq), const_cast<float *>(a.yt));
         sl = SelectDesc{a.rec, x.k, x.p.delta, x.rot, res_dev + i, status_dev + i};
     }
-    int32_t header[2] = {n_items, count};
+    int32_t header[3] = {n_items - n_general, count, n_items};
     DSES_HIP(hipMemcpyAsync(b->inst.ptr, inst.data(), inst.size() * sizeof(SweepArgs),
                             hipMemcpyHostToDevice, stream));
     DSES_HIP(hipMemcpyAsync(b->stage.ptr, stage.data(), stage.size() * sizeof(StageDesc),
@@ -574,7 +591,8 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         DSES_HIP(hipEventCreate(&t1));
         auto time_layout = [&](const Layout &L, float *ms) -> dses_status {
             build_items(L.items_per_cu, &items);
-            header[0] = (int32_t)items.size();
+            header[0] = (int32_t)items.size() - n_general;
+            header[2] = (int32_t)items.size();
             for (int i = 0; i < count; ++i) inst[i].vote_parts = L.vote_parts;
             DSES_HIP(hipMemcpyAsync(b->items.ptr, items.data(), items.size() * sizeof(BatchItem),
                                     hipMemcpyHostToDevice, stream));
@@ -582,11 +600,15 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                                     stream));
             DSES_HIP(hipMemcpyAsync(b->inst.ptr, inst.data(), count * sizeof(SweepArgs),
                                     hipMemcpyHostToDevice, stream));
-            DSES_HIP(launch_clear(cursor, 1, stream));
+            DSES_HIP(launch_clear(cursor, 2, stream));
             DSES_HIP(hipEventRecord(t0, stream));
             BatchArgs ba{static_cast<SweepArgs *>(b->inst.ptr),
                          static_cast<BatchItem *>(b->items.ptr), hdr_dev, cursor, nullptr};
-            DSES_HIP(launch_sweep_batch(ba, batch_scorer, grid, stream));
+            DSES_HIP(launch_sweep_batch(ba, batch_scorer, false, grid, stream));
+            if (n_general > 0) {
+                ba.cursor = cursor + 1;
+                DSES_HIP(launch_sweep_batch(ba, batch_scorer, true, grid, stream));
+            }
             DSES_HIP(hipEventRecord(t1, stream));
             DSES_HIP(hipStreamSynchronize(stream));
             DSES_HIP(hipEventElapsedTime(ms, t0, t1));
@@ -621,7 +643,8 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         // restore the chosen layout for the run below
         build_items(lay.items_per_cu, &items);
         n_items = (int)items.size();
-        header[0] = n_items;
+        header[0] = n_items - n_general;
+        header[2] = n_items;
         for (int i = 0; i < count; ++i) inst[i].vote_parts = lay.vote_parts;
         DSES_HIP(hipMemcpyAsync(b->items.ptr, items.data(), items.size() * sizeof(BatchItem),
                                 hipMemcpyHostToDevice, stream));
@@ -643,8 +666,8 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         DSES_HIP(hipEventRecord(e0, stream));
     }
     if (o.use_graph) {
-        if ((st = run_graph(b, batch_scorer, grid, stream)) != DSES_OK) return st;
-    } else if ((st = enqueue_batch(b, batch_scorer, grid, stream)) != DSES_OK) {
+        if ((st = run_graph(b, batch_scorer, n_general > 0, grid, stream)) != DSES_OK) return st;
+    } else if ((st = enqueue_batch(b, batch_scorer, n_general > 0, grid, stream)) != DSES_OK) {
         return st;
     }
     if (timing) DSES_HIP(hipEventRecord(e1, stream));

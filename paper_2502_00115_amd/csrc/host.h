@@ -142,6 +142,21 @@ constexpr float kSrcCoordLimit = 1.0e4f;
 int counter_bits_for(int64_t bound, int32_t n, int32_t m, const Params &p);
 dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, int counter_bits,
                       Geom *g);
+// Reference points per lane group of the windowed vote (32 or 64; `asked` if not 0,
+// 16 taken as 32), or 0 where only the general path applies: sources not sorted, or
+// x planes wider than its 16-bit strides.
+int choose_gref(const Geom &g, bool sorted, float x_extent, int asked);
+// The same for the batched kernels, which hold fewer of the layouts: groups of 32 or 64
+// points under 16-bit counters, of 64 under 32-bit ones.
+inline int choose_batch_gref(const Geom &g, bool sorted, float x_extent)
+{
+    const int gref = choose_gref(g, sorted, x_extent, 0);
+    return gref != 0 && g.counter_bits == 32 ? 64 : gref;
+}
+// Staging of a reference of g.m points for a vote of geometry g with lane groups of
+// gref points (0: the general path).
+StageDesc stage_desc(const Geom &g, int gref, const float *tgt, const int32_t *perm,
+                     int32_t *yq, float *yt);
 // Upper bound on any bin's vote count (decides 16- vs 32-bit LDS counters):
 // n x the largest reference population of a 2 x 2 x 2 block of cells of pitch
 // slightly above delta (for a fixed source point, the pairs sharing a bin have
@@ -197,10 +212,9 @@ struct TargetRes {
     struct Stage {                           // staged copy for one (delta, box)
         float delta;
         int32_t klo[3];
-        int32_t *yq;                         // fixed-point copy (4 m int32)
+        int32_t zbits, gref;                 // the layout it is staged for
+        int32_t *yq;                         // fixed-point copy (stage_words(m) int32)
         float *yt;
-        bool sorted;                         // ref_x_range succeeded
-        int32_t ylo = 0, yhi = 0;            // its result
     };
     std::deque<Stage> stages;                // deque: references survive push_back
     struct Population {                      // ref_block_population for (delta, box)
@@ -264,12 +278,16 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
 void add_stats(Context *c, double vote_ms, double score_ms, double select_ms, double stage_ms,
                int64_t launches, int64_t pairs_voted, int64_t pairs_scored, int64_t cands);
 
-// Stage a resident target for lattice pitch p.delta / box p.klo (cached; holds
-// tm->grid_mu while building; synchronous on `stream`).
 // ref_block_population of a resident target, cached per (delta, box).
 int64_t target_block_population(TargetRes *tm, const Params &p);
-dses_status ensure_target_stage(TargetRes *tm, const Params &p, hipStream_t stream,
-                                const TargetRes::Stage **out);
+// x range of a resident target's staged fixed-point coordinates at pitch p.delta and
+// box p.klo (sorting the reference on first use); false if the sorted vote cannot
+// be used.
+bool target_x_range(TargetRes *tm, const Params &p, int32_t *ylo, int32_t *yhi);
+// Stage a resident target for geometry g and lane groups of gref points (cached by
+// pitch, box and layout; holds tm->grid_mu while building; synchronous on `stream`).
+dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, int gref,
+                                hipStream_t stream, const TargetRes::Stage **out);
 // Build (or reuse) the resident target's cell grid for radius r; fills cg.
 dses_status ensure_target_grid(TargetRes *tm, float r, CellGrid *cg);
 

@@ -30,6 +30,7 @@ struct Geom {
     int32_t size[3];       // bins per axis
     int32_t metric;        // dses_metric
     float lp;              // exponent of DSES_TRUNC_LP
+    int32_t zbits;         // fraction bits of the z lattice: 15 with 16-bit counters, else 16
     int32_t counter_bits;  // 16: two counters per LDS word (z rows padded to even), 32: one
     int32_t row_words;     // LDS words per z row: (size_z + 1) / 2 or size_z
     int32_t pps;           // x-planes per LDS slab
@@ -69,37 +70,18 @@ __host__ __device__ inline int vote_parts_auto(int groups)
     const int g = 64 / (groups > 0 ? groups : 1);
     return g < 1 ? 1 : (g > 8 ? 8 : g);
 }
-// Lane groups of the sorted-source vote: 2^(lg+1) reference points (64, 32 or
-// 16), two per lane on 2^lg lanes, repeated on the wave's 64 >> lg lane
-// sub-groups, which take alternate 4-source pieces of the same stream window, so
-// a wave step covers 2^(lg+1) points x (64 >> lg) sources.  Smaller groups span
-// less x, so their windows carry less slack (about 2^(lg+1) * X source-bins per
-// slab over all groups, X the reference's x extent in bins), but there are more
-// work units, each costing about kUnitSteps wave steps of set-up, padding and
-// slab-end imbalance (fitted); rho = n / (X + size_x) sources per bin turns a step
-// into 64 / rho source-bins.  The size with the least modelled cost wins (ties:
-// the larger group).  It picks 16 points for a 717-point source against a
-// 1,024-point reference with eps 0.03 and 64 for 64 / 256 points and for 4,096 /
-// 16,384 points.
-constexpr float kUnitSteps = 4.9f;
-__host__ __device__ inline int lane_group_log2(int m, int n, int size_x, float x_extent,
-                                               int vote_parts)
+// The windowed vote's parts per lane group, as a power of two: `asked` rounded down,
+// or about kVoteUnits units per slab for the 16 waves (at most 8 parts).
+constexpr int kVoteUnits = 96;
+__host__ __device__ inline int parts_log2(int groups, int asked)
 {
-    const float per_unit = kUnitSteps * 64.0f * (x_extent + (float)size_x) /
-                           (float)(n > 0 ? n : 1);
-    int best = 5;
-    float best_cost = 0.0f;
-    for (int lg = 5; lg >= 3; --lg) {
-        const int gref = 2 << lg;
-        const int groups = (m + gref - 1) / gref;
-        const int parts = vote_parts > 0 ? vote_parts : vote_parts_auto(groups);
-        const float cost = (float)gref * x_extent + per_unit * (float)(groups * parts);
-        if (lg == 5 || cost < best_cost) {
-            best_cost = cost;
-            best = lg;
-        }
+    int l = 0;
+    if (asked > 0) {
+        while (l < 4 && (2 << l) <= asked) ++l;
+        return l;
     }
-    return best;
+    while (l < 3 && (groups << (l + 1)) <= kVoteUnits) ++l;
+    return l;
 }
 constexpr int kUnitCounter = 128;       // LDS scratch word: next vote work unit
 constexpr int kSrcBmin = 129;           // LDS scratch words: lowest and highest occupied
@@ -116,8 +98,8 @@ constexpr int kExhaustiveMaxSrc = 12288;
 struct SweepArgs {
     const float *src;      // n x 3 AoS
     const float *rot;      // K x 9
-    const int32_t *yq;     // fixed-point reference (lattice offset folded in), sorted by x:
-                           // four arrays of m, x, y, z at 2^-16 bins and z at 2^-15 bins
+    const int32_t *yq;     // fixed-point reference (lattice offset folded in), sorted by x: x, y,
+                           // z arrays of m, then the x range of each lane group
     const float *yt;       // reference, SoA (3 * m), same order
     int32_t *scratch;      // per workgroup slot: the rotation's sources sorted by x (below)
     int64_t scratch_stride;   // sources a slot holds (>= n)
@@ -129,8 +111,7 @@ struct SweepArgs {
     dses_record *rec;      // one record per rotation index
     int32_t k;             // rotations
     int32_t vote_parts;    // stream-window parts per lane group (0: vote_parts_auto)
-    int32_t lane_group;    // reference points per lane group: 16, 32, 64 (0: lane_group_log2)
-    float ref_x_extent;    // x extent of the scaled reference in bins (lane-group choice)
+    int32_t gref;          // reference points per lane group: 32 or 64; 0: general path
 };
 
 // Scratch slot of one workgroup (int32 words): rotated fixed-point sources sorted
@@ -156,7 +137,8 @@ struct BatchItem {
 struct BatchArgs {
     const SweepArgs *inst;     // per-instance sweep arguments (device)
     const BatchItem *items;    // work list, most expensive first
-    const int32_t *header;     // header[0] = items, header[1] = instances
+    const int32_t *header;     // [0] items of the windowed vote, [1] instances, [2] all items
+                               // (the general path's follow the windowed ones)
     uint32_t *cursor;          // work-list cursor, cleared before each launch
     int32_t *scratch;          // if set: this launch's source-sort scratch (overrides
                                // the instances' own, so concurrent launches never share),
@@ -178,9 +160,15 @@ struct StageDesc {
     int32_t m;
     double S16, S15;
     int32_t klo[3];
-    int32_t *yq;
+    int32_t zbits;         // fraction bits of the staged z
+    int32_t gref;          // points per lane group (64 in the general path)
+    int32_t *yq;           // stage_words(m) int32
     float *yt;
 };
+
+// int32 words of a staged fixed-point reference: x, y and z, then the x range of each
+// lane group.
+__host__ __device__ inline size_t stage_words(size_t m) { return 3 * m + 2 * ((m + 31) / 32); }
 
 struct SelectDesc {
     const dses_record *rec;
@@ -214,8 +202,7 @@ struct CheckArgs {
 
 // Launchers (defined in kernels.hip); all enqueue on `stream`.
 hipError_t launch_check(const CheckArgs &a, hipStream_t stream);
-hipError_t launch_stage(const float *tgt, const int32_t *perm, int32_t m, double S16, double S15,
-                        const int32_t *klo, int32_t *yq, float *yt, hipStream_t stream);
+hipError_t launch_stage(const StageDesc &d, hipStream_t stream);
 hipError_t launch_sweep(const SweepArgs &a, int scorer, int grid, hipStream_t stream);
 hipError_t launch_select(const dses_record *rec, int32_t k, const float *rot, float delta,
                          DevResult *res, const uint32_t *status, hipStream_t stream);
@@ -233,7 +220,9 @@ hipError_t launch_score_pruned(const SweepArgs &a, int scorer, float q, uint32_t
 // BRUTE or GRID scorer): one record per rotation with its best translation.
 hipError_t launch_exhaustive(const SweepArgs &a, int scorer, int grid, hipStream_t stream);
 hipError_t launch_clear(uint32_t *p, int32_t words, hipStream_t stream);
-hipError_t launch_sweep_batch(const BatchArgs &b, int scorer, int grid, hipStream_t stream);
+// general: the items past header[0], which need the general path.
+hipError_t launch_sweep_batch(const BatchArgs &b, int scorer, bool general, int grid,
+                              hipStream_t stream);
 // which = 0: batched staging, 1: batched selection
 hipError_t launch_batch_aux(const StageDesc *stage, const SelectDesc *sel, const int32_t *header,
                             int max_count, int which, hipStream_t stream);

@@ -6,22 +6,23 @@
 //    lattice (2^-16 bins, the lattice offset folded into the reference) and
 //    bucket-sorted by x into a per-workgroup scratch slot (an x array, a 64-bit
 //    (y, z) array and a bucket table).
-//  * In the vote each lane holds two points of the x-sorted reference (a work
-//    unit's lane group: 64, 32 or 16 consecutive points, the smaller groups
-//    repeated on the wave's lane sub-groups) and streams the sources of the
-//    window whose pairs can land in the current slab; the sub-groups take
-//    alternate 4-source pieces of it.  Sources arrive through 16-byte buffer
-//    loads (one address per sub-group), two blocks in flight.  A pair's bin is
-//    exact integer arithmetic: one 64-bit add for the y and z differences, one
-//    subtraction for x, the bin being the high 16 bits of each.
+//  * In the vote each lane holds two or four points of the x-sorted reference (a work
+//    unit's lane group of 32 or 64 consecutive points on 16 lanes, repeated on the
+//    wave's four lane sub-groups) and streams the sources of the window whose pairs
+//    can land in the current slab; the sub-groups take alternate 4-source pieces of
+//    it.  Sources arrive through 16-byte buffer loads (one address per sub-group), two
+//    blocks in flight.  A pair's bin is exact integer arithmetic: one 64-bit add for
+//    the y and z differences, one subtraction for x, the bin being the high 16 bits
+//    of each.
 //  * The vote array of Alg. 2 lives in LDS, in x-slabs that each fit it, as
 //    16-bit counters packed two per 32-bit word (incremented with ds_add_u32 of
 //    1 or 1<<16) or as 32-bit counters.  16-bit counters are used only when the
 //    host has proven that no bin can reach 2^16 votes (counter_bound in
 //    api.hip), and 32-bit ones also when every slab carries at least 2^20 pairs
 //    (counter_bits_for), where the cheaper pairs outweigh the extra slabs.
-//  * The mode per slab: the largest count by a packed 16-bit max over the slab,
-//    then, only when it beats the earlier slabs, its lowest linear index.
+//  * The mode per slab: the slab is read into registers and cleared in one pass; the
+//    largest count by a packed 16-bit max, then, only when it beats the earlier slabs
+//    and only in the waves that hold it, its lowest linear index.
 //  * Scoring rotates the sources again, in input order; the error sum is a
 //    fixed-order tree, so a rotation's record does not depend on what else runs
 //    on the GPU.
@@ -167,37 +168,60 @@ __device__ __forceinline__ void rotate_quant(const float *R, float x, float y, f
     Pz = quant_src(__dmul_rn(p2, Sz));
 }
 
+// Wave64 maximum / minimum of an unsigned value by DPP lane moves (no LDS round
+// trip): pairs and quads by quad permutations, eight and sixteen lanes by the
+// half-row and row mirrors, then row 0 into row 1 and row 2 into row 3
+// (row_bcast:15), rows 0-1 into rows 2-3 (row_bcast:31); lane 63 holds the
+// result, read back as a wave-uniform value.  Lanes a move does not write keep
+// the identity, so inactive sources never change the result.
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_ext_u32(uint32_t v)
+{
+    const int id = MAX ? 0 : -1;
+    auto op = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0xB1, 0xF, 0xF, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x4E, 0xF, 0xF, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x141, 0xF, 0xF, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x140, 0xF, 0xF, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x142, 0xA, 0xF, false));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x143, 0xC, 0xF, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return wave_ext_u32<true>(v); }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return wave_ext_u32<false>(v); }
+
 // --------------------------------------------------------------------------
 // staging: reference AoS -> SoA float (scoring) and the fixed-point copy used
-// for binning, four arrays of m: x, y, z at 2^-16 bins and z at 2^-15 bins,
-//   Y_a = q(y_a) with the offset (1/2 - k_lo_a) 2^F folded in.
+// for binning, three arrays of m: x and y at 2^-16 bins, z at 2^-zbits bins,
+//   Y_a = q(y_a) with the offset (1/2 - k_lo_a) 2^F folded in,
+// then the x range of every lane group of gref consecutive points (two int32 each).
 // --------------------------------------------------------------------------
-__device__ __forceinline__ void stage_point(const float *tgt, int src, int j, int32_t m,
-                                            double S16, double S15, const int32_t *klo,
-                                            int32_t *yq, float *yt)
+__device__ __forceinline__ void stage_point(const StageDesc &d, int j)
 {
+    const int src = d.perm ? d.perm[j] : j;
+    int32_t q[3];
     for (int a = 0; a < 3; ++a) {
-        const float y = tgt[3 * src + a];
-        yq[a * m + j] = quant_ref(y, S16, (0.5 - (double)klo[a]) * 65536.0);
-        yt[a * m + j] = y;
+        const float y = d.tgt[3 * src + a];
+        q[a] = a == 2 && d.zbits == 15
+                   ? quant_ref(y, d.S15, (0.5 - (double)d.klo[a]) * 32768.0)
+                   : quant_ref(y, d.S16, (0.5 - (double)d.klo[a]) * 65536.0);
+        d.yq[a * d.m + j] = q[a];
+        d.yt[a * d.m + j] = y;
     }
-    yq[3 * m + j] = quant_ref(tgt[3 * src + 2], S15, (0.5 - (double)klo[2]) * 32768.0);
+    int32_t *gx = d.yq + 3 * (size_t)d.m + 2 * (size_t)(j / d.gref);
+    if (j % d.gref == 0) gx[0] = q[0];                  // the points are sorted by x
+    if (j % d.gref == d.gref - 1 || j == d.m - 1) gx[1] = q[0];
 }
 
-__global__ void k_stage(const float *tgt, const int32_t *perm, int32_t m, double S16, double S15,
-                        int32_t klo0, int32_t klo1, int32_t klo2, int32_t *yq, float *yt)
+__global__ void k_stage(StageDesc d)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    const int32_t klo[3] = {klo0, klo1, klo2};
-    stage_point(tgt, perm ? perm[j] : j, j, m, S16, S15, klo, yq, yt);
+    if (j < d.m) stage_point(d, j);
 }
 
-hipError_t launch_stage(const float *tgt, const int32_t *perm, int32_t m, double S16, double S15,
-                        const int32_t *klo, int32_t *yq, float *yt, hipStream_t stream)
+hipError_t launch_stage(const StageDesc &d, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_stage, dim3((m + 255) / 256), dim3(256), 0, stream, tgt, perm, m, S16,
-                       S15, klo[0], klo[1], klo[2], yq, yt);
+    hipLaunchKernelGGL(k_stage, dim3((d.m + 255) / 256), dim3(256), 0, stream, d);
     return hipGetLastError();
 }
 
@@ -241,6 +265,22 @@ __device__ __forceinline__ T kload(const T *p)
     return v;
 }
 
+// The sweep's arguments for one phase of a rotation (sort, vote, scan, score), read
+// again where the phase begins: kept over a whole rotation, the arguments of every
+// phase together take more scalar registers than there are.
+__device__ __forceinline__ SweepArgs phase_args(const SweepArgs *p)
+{
+    asm volatile("" : "+s"(p));
+    return kload(p);
+}
+
+// Rotation k of the list.
+__device__ __forceinline__ void load_rotation(const SweepArgs &a, int k, float *R)
+{
+#pragma unroll
+    for (int e = 0; e < 9; ++e) R[e] = kc(a.rot)[9 * (size_t)k + e];
+}
+
 // Lane layout for a chunk of up to 1024 source points: `sw` waves hold the chunk
 // (one point per lane) and the reference is split into G partitions, one per
 // group of sw waves, when the chunk is small.
@@ -280,6 +320,7 @@ struct VoteConst {
     uint32_t npx, syx, szx;    // range limits: np << 16, S_y << 16, S_z << Fz
     uint32_t sx, sy;           // x and y strides: bytes (sx4, sy4), or words when WIDE
     uint32_t base;             // LDS byte address of the slab's first counter
+    uint32_t half, k16;        // 16-bit counters: 0x8000 and the float 65535 / 32768
 };
 
 #define DSES_VP_X "v_cmpx_gt_u32 vcc, %[npx], %[dx]\n\t"
@@ -296,17 +337,20 @@ struct VoteConst {
     "v_mad_u32_u16 %[t1], %[dx], %[sx], %[t1] op_sel:[1,0,0,0]\n\t"                           \
     "v_lshl_add_u32 %[t1], %[t1], 2, %[base]\n\t"
 #define DSES_VP_HALF                                                                         \
-    "v_bfe_u32 %[t2], %[dz], 15, 1\n\t"                                                      \
-    "v_mad_u32_u24 %[t2], %[t2], %[ffff], 1\n\t"
-// 16-bit counters: the increment t2 is computed in the block; 32-bit: it is 1
+    "v_and_b32 %[t2], %[half], %[dz]\n\t"                                                  \
+    "v_fma_f32 %[t2], %[t2], %[k16], 1\n\t"
+// 16-bit counters: the increment t2 is computed in the block, 1 or 65536 from bit 15
+// of D_z (that bit as a subnormal float, an integer, times 65535 / 32768 plus one
+// unit is exact; with vector operands both instructions issue at twice the rate of
+// a bit-field extract and an integer multiply-add); 32-bit: it is 1
 #define DSES_VP_OPERANDS                                                                     \
-    [dx] "v"(dx), [dy] "v"(dy), [dz] "v"(dz), [npx] "s"(v.npx), [syx] "s"(v.syx),            \
-        [szx] "s"(v.szx), [sx] "s"(v.sx), [sy] "s"(v.sy), [base] "s"(v.base)
+    [dx] "v"(dx), [dy] "v"(dy), [dz] "v"(dz), [npx] "v"(v.npx), [syx] "v"(v.syx),            \
+        [szx] "v"(v.szx), [sx] "s"(v.sx), [sy] "s"(v.sy), [base] "s"(v.base)
 #define DSES_VP_ASM16(TEXT)                                                                  \
     asm volatile("s_mov_b64 %[save], exec\n\t" TEXT "ds_add_u32 %[t1], %[t2]\n\t"            \
                  "s_mov_b64 exec, %[save]"                                                   \
                  : [save] "=&s"(save), [t1] "=&v"(t1), [t2] "=&v"(t2)                          \
-                 : DSES_VP_OPERANDS, [ffff] "s"(0xFFFFu)                                      \
+                 : DSES_VP_OPERANDS, [half] "v"(v.half), [k16] "v"(v.k16)                                     \
                  : "vcc", "memory")
 #define DSES_VP_ASM32(TEXT)                                                                  \
     asm volatile("s_mov_b64 %[save], exec\n\t" TEXT "ds_add_u32 %[t1], %[t2]\n\t"            \
@@ -626,41 +670,42 @@ __device__ __forceinline__ void src_window(const SweepArgs &a, __amdgpu_buffer_r
     ihi = bie <= bif ? ilo : (bie > bmax ? a.g.n : tie);
 }
 
-// Votes of all pairs whose bin falls in the box x-planes [x0, x0 + np) into the
-// LDS counters.  Work units are (lane group, part of the group's stream range),
-// G parts per group; waves take units one at a time from an LDS counter
-// (cleared with the slab), so a wave whose ranges were short takes more units
-// instead of idling at the slab's closing barrier.
-//   sorted: a lane group is 2^(lg+1) consecutive points of the x-sorted
-//           reference, two per lane (points j and j + 2^lg of the group for lane
-//           j), held by each of the wave's 64 >> lg lane sub-groups; the stream is
-//           the window of the rotation's x-sorted sources, padded to a multiple
-//           of 4 and taken in blocks of B = 256 >> lg sources (sub-group h takes
-//           4h .. 4h + 3) plus a strided tail (vote_span_lanes);
+// The general path's votes of all pairs whose bin falls in the box x-planes [x0,
+// x0 + np) into the LDS counters: planes of any width, sources of any number.  Work
+// units are (lane group, part of the group's stream range), G parts per group; waves
+// take units one at a time from an LDS counter (cleared with the slab).
+//   sorted: a lane group is 64 consecutive points of the x-sorted reference, two per
+//           lane (points j and j + 32), held by both half waves; the stream is the
+//           window of the rotation's x-sorted sources, padded to a multiple of 4 and
+//           taken in blocks of 8 (half h takes 4h .. 4h + 3) plus a strided tail
+//           (vote_span_lanes);
 //   else:   lanes hold 64 rotated sources, the stream is the whole reference.
-// lg is a template constant (one instantiation per lane-group size): as a
-// run-time value it cost 1.5% of the sweep.
-template <int CW, int LG, bool SORTED, bool WIDE>
-__device__ void vote_slab(const SweepArgs &a, const float *R, int x0, int np, uint32_t *hist,
-                          int slot)
+template <int CW, bool SORTED, bool WIDE>
+__device__ __forceinline__ void vote_slab(const SweepArgs *args, int32_t *sp, int k, int x0,
+                                          int np, uint32_t *hist)
 {
+    const SweepArgs a = phase_args(args);
     const Geom &g = a.g;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t Sy = g.size[1], Sz = g.size[2];
     const uint32_t syw = (uint32_t)g.row_words, sxw = syw * Sy;
     VoteConst v;
-    v.npx = (uint32_t)np << 16;
-    v.syx = Sy << 16;
-    v.szx = Sz << (CW == 16 ? 15 : 16);
+    // in vector registers: with a scalar operand an instruction issues at half the rate
+    // or a little slower
+    asm("v_mov_b32 %0, %1" : "=v"(v.npx) : "s"((uint32_t)np << 16));
+    asm("v_mov_b32 %0, %1" : "=v"(v.syx) : "s"(Sy << 16));
+    asm("v_mov_b32 %0, %1" : "=v"(v.szx) : "s"(Sz << (CW == 16 ? 15 : 16)));
     v.sx = WIDE ? sxw : 4u * sxw;
     v.sy = WIDE ? syw : 4u * syw;
     v.base = (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t *)hist;
+    // in vector registers: the increment's two instructions run at the full rate there
+    asm("v_mov_b32 %0, 0x8000" : "=v"(v.half));
+    asm("v_mov_b32 %0, 0x3fffff00" : "=v"(v.k16));
     const uint32_t xofs = (uint32_t)x0 << 16;
     const int m = g.m;
-    const int zsel = CW == 16 ? 3 : 2;         // the reference's z array for this width
     uint32_t *ctr = hist + kHistWordsMax + kUnitCounter;
     if (SORTED) {
-        constexpr int lg = LG;
+        constexpr int lg = 5;
         const int gsz = 1 << lg;               // lanes per copy of the group
         const int gref = 2 * gsz;              // reference points per group
         const int B = 256 >> lg;
@@ -672,10 +717,9 @@ __device__ void vote_slab(const SweepArgs &a, const float *R, int x0, int np, ui
         // nb <= kSortMax / 4 and p * gmul < 8192, so the product stays below 2^32
         const uint32_t gmul = 8192u / (uint32_t)G;
         const int64_t ns = src_stride(a.scratch_stride);
-        const int32_t *sp = a.scratch + (size_t)slot * slot_words(a.scratch_stride);
         const f4u sdesc = desc_words(sp, 12 * ns);
         const __amdgpu_buffer_rsrc_t srs = rsrc(sp, 12 * ns);
-        const __amdgpu_buffer_rsrc_t yrs = rsrc(a.yq, 16 * (int64_t)m);
+        const __amdgpu_buffer_rsrc_t yrs = rsrc(a.yq, 12 * (int64_t)m);
         const __amdgpu_buffer_rsrc_t trs = rsrc(sp + 3 * ns, 4 * (kSrcBuckets + 1));
         const uint32_t *scr = hist + kHistWordsMax;
         const int bmin = (int)__builtin_amdgcn_readfirstlane(scr[kSrcBmin]);
@@ -692,9 +736,9 @@ __device__ void vote_slab(const SweepArgs &a, const float *R, int x0, int np, ui
             const uint32_t yo0 = 4u * (uint32_t)min(j, m - 1);
             const uint32_t yo1 = 4u * (uint32_t)min(j + gsz, m - 1);
             uint32_t x0 = load1(yrs, yo0, 0), y0 = load1(yrs, yo0, 4 * m);
-            uint32_t z0 = load1(yrs, yo0, 4 * zsel * m);
+            uint32_t z0 = load1(yrs, yo0, 8 * m);
             uint32_t x1 = load1(yrs, yo1, 0), y1 = load1(yrs, yo1, 4 * m);
-            uint32_t z1 = load1(yrs, yo1, 4 * zsel * m);
+            uint32_t z1 = load1(yrs, yo1, 8 * m);
             if (j >= m) x0 = y0 = z0 = kPadRef;
             if (j + gsz >= m) x1 = y1 = z1 = kPadRef;
             LanePts L;
@@ -733,10 +777,12 @@ __device__ void vote_slab(const SweepArgs &a, const float *R, int x0, int np, ui
         const int nsg = (g.n + 63) >> 6;
         const int G = a.vote_parts > 0 ? a.vote_parts : vote_parts_auto(nsg);
         const int total = nsg * G;
-        const f4u rdesc = desc_words(a.yq, 16 * (int64_t)m);
-        const __amdgpu_buffer_rsrc_t rrs = rsrc(a.yq, 16 * (int64_t)m);
-        const SoaOffs so = soa_offs(m, zsel);
+        const f4u rdesc = desc_words(a.yq, 12 * (int64_t)m);
+        const __amdgpu_buffer_rsrc_t rrs = rsrc(a.yq, 12 * (int64_t)m);
+        const SoaOffs so = soa_offs(m, 2);
         const double Sz = CW == 16 ? g.S15 : g.S16;
+        float R[9];
+        load_rotation(a, k, R);
         for (;;) {
             int u = 0;
             if (lane == 0) u = (int)atomicAdd(ctr, 1u);
@@ -763,6 +809,225 @@ __device__ void vote_slab(const SweepArgs &a, const float *R, int x0, int np, ui
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // asm-issued LDS atomics
 }
 
+// --------------------------------------------------------------------------
+// The windowed vote: lanes hold points of the x-sorted reference, the rotation's
+// x-sorted sources stream past them.
+//
+// A lane group is GREF = 32 or 64 consecutive reference points on 16 lanes, two or
+// four points per lane, repeated on the wave's four lane sub-groups, which take
+// different sources of the same window: a wave step votes GREF x 4 pairs, and the 48
+// bytes a lane loads for four sources serve 8 or 16 pairs (the vector-memory return
+// path took as long as the vote's arithmetic with two points on each of 32 lanes).
+// The sub-groups are the even and the odd lanes of the two half waves: those are the
+// lane sets inside which LDS resolves bank conflicts, so each set accesses the
+// counters of 16 points of the group against one source.
+//
+// Bound by vector instruction issue: 7 (32-bit counters) or 9 instructions per pair,
+// about 30 or 35 cycles of a SIMD per 64 pairs, against 7.6-7.9 measured x 4 SIMDs
+// with everything else of the rotation (4,000 x 8,192 and 4,096 x 16,384 points).
+// --------------------------------------------------------------------------
+template <int GREF>
+struct Shape {
+    static constexpr int lanes = 16;                        // per copy of the group
+    static constexpr int pts = GREF / lanes;                // points per lane
+    static constexpr int subs = 64 / lanes;                 // sub-groups of a wave
+    static constexpr int block = 4 * subs;                  // sources per streamed block
+    static constexpr int tail_steps = (block - 4) / subs;
+    __device__ static __forceinline__ int point(int lane) { return (lane >> 1) & (lanes - 1); }
+    __device__ static __forceinline__ int sub(int lane) { return (lane >> 5) * 2 + (lane & 1); }
+};
+
+// A lane's points: x, and y and z as one 64-bit value (y << 32) | (z + 2^31).
+template <int P>
+struct LanePoints {
+    uint32_t x[P];
+    uint64_t yz[P];
+};
+
+template <int CW, bool XT, int P>
+__device__ __forceinline__ void vote_block(f4u x, f4u yz01, f4u yz23, const LanePoints<P> &L,
+                                           const VoteConst &v)
+{
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2 n01 = __builtin_bit_cast(u64x2, yz01), n23 = __builtin_bit_cast(u64x2, yz23);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint64_t nq = q < 2 ? n01[q] : n23[q - 2];
+        uint32_t dx[P];
+        uint64_t e[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            dx[p] = L.x[p] - x[q];
+            e[p] = add64(L.yz[p], nq);
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            vote_pair<CW, false, XT>(dx[p], (uint32_t)(e[p] >> 32), (uint32_t)e[p], v);
+    }
+}
+
+// Windows of one chunk of 64 lane groups, lane = group: the window's first source,
+// its length (a multiple of 4 inside the padded arrays) and its interior in the same
+// multiples.
+struct Windows {
+    int lo, len, i0, i1;
+};
+
+__device__ __forceinline__ Windows group_windows(const SweepArgs &a, __amdgpu_buffer_rsrc_t gxs,
+                                                 __amdgpu_buffer_rsrc_t trs, int chunk, int ngr,
+                                                 int bmin, int bmax, int32_t xofs, int np, int ns)
+{
+    const int g = chunk * 64 + (int)(threadIdx.x & 63);
+    const uint32_t go = 8u * (uint32_t)min(g, ngr - 1);
+    const int32_t ymin = (int32_t)load1(gxs, go, 0) - xofs;
+    const int32_t ymax = (int32_t)load1(gxs, go, 4) - xofs;
+    int lo, hi, ilo, ihi;
+    src_window(a, trs, bmin, bmax, ymin, ymax, np, lo, hi, ilo, ihi);
+    hi = max(hi, lo);
+    Windows w;
+    w.len = (hi - lo + 3) & ~3;
+    hi = min(ns, lo + w.len);
+    w.lo = hi - w.len;
+    w.i0 = w.lo + ((max(ilo, w.lo) - w.lo + 3) & ~3);
+    w.i1 = w.lo + ((min(ihi, hi) - w.lo) & ~3);
+    if (w.i1 <= w.i0) w.i0 = w.i1 = hi;
+    return w;
+}
+
+// Votes of all pairs whose bin falls in the box x-planes [x0, x0 + np) into the LDS
+// counters.  Work units are (lane group, one of G parts of its window); the waves
+// take them one at a time from an LDS counter, because the SIMDs favour their older
+// waves: with equal shares fixed in advance the oldest of four waves was done after
+// half the slab's time.  A wave computes the windows of 64 groups at once, lane =
+// group, when it first needs one of them, so that a unit starts with one memory
+// round trip (its reference points beside its first sources).
+template <int CW, int GREF>
+__device__ __forceinline__ void vote_windows(const SweepArgs *args, int32_t *sp, int x0, int np,
+                                             uint32_t *hist)
+{
+    using S = Shape<GREF>;
+    const SweepArgs a = phase_args(args);
+    const Geom &g = a.g;
+    const int lane = threadIdx.x & 63;
+    const uint32_t Sy = g.size[1], Sz = g.size[2];
+    const uint32_t syw = (uint32_t)g.row_words;
+    VoteConst v;
+    // in vector registers: with a scalar operand an instruction issues at half the rate
+    // or a little slower
+    asm("v_mov_b32 %0, %1" : "=v"(v.npx) : "s"((uint32_t)np << 16));
+    asm("v_mov_b32 %0, %1" : "=v"(v.syx) : "s"(Sy << 16));
+    asm("v_mov_b32 %0, %1" : "=v"(v.szx) : "s"(Sz << (CW == 16 ? 15 : 16)));
+    v.sx = 4u * syw * Sy;
+    v.sy = 4u * syw;
+    v.base = (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t *)hist;
+    asm("v_mov_b32 %0, 0x8000" : "=v"(v.half));
+    asm("v_mov_b32 %0, 0x3fffff00" : "=v"(v.k16));
+    const int32_t xofs = x0 << 16;
+    const int m = g.m, ngr = (m + GREF - 1) / GREF;
+    const int ns = (int)src_stride(a.scratch_stride);
+    const f4u sdesc = desc_words(sp, 12 * (int64_t)ns);
+    const __amdgpu_buffer_rsrc_t srs = rsrc(sp, 12 * (int64_t)ns);
+    const __amdgpu_buffer_rsrc_t yrs = rsrc(a.yq, 12 * (int64_t)m);
+    const __amdgpu_buffer_rsrc_t gxs = rsrc(a.yq + 3 * (int64_t)m, 8 * (int64_t)ngr);
+    const __amdgpu_buffer_rsrc_t trs = rsrc(sp + 3 * (int64_t)ns, 4 * (kSrcBuckets + 1));
+    const uint32_t *scr = hist + kHistWordsMax;
+    const int bmin = (int)__builtin_amdgcn_readfirstlane(scr[kSrcBmin]);
+    const int bmax = (int)__builtin_amdgcn_readfirstlane(scr[kSrcBmax]);
+    const uint32_t hoff = 16u * (uint32_t)S::sub(lane), hoff2 = 2u * hoff;
+    const int pt = S::point(lane);
+
+    const int lgp = parts_log2(ngr, a.vote_parts);
+    const int units = ngr << lgp;
+    uint32_t *ctr = hist + kHistWordsMax + kUnitCounter;
+    Windows w = group_windows(a, gxs, trs, 0, ngr, bmin, bmax, xofs, np, ns);
+    int chunk = 0;
+    for (;;) {
+        int u = 0;
+        if (lane == 0) u = (int)atomicAdd(ctr, 1u);
+        u = uni(u);
+        if (u >= units) break;
+        const int gi = u >> lgp, part = u & ((1 << lgp) - 1);
+        if ((gi >> 6) != chunk) {
+            chunk = gi >> 6;
+            w = group_windows(a, gxs, trs, chunk, ngr, bmin, bmax, xofs, np, ns);
+        }
+        LanePoints<S::pts> L;
+#pragma unroll
+        for (int p = 0; p < S::pts; ++p) {
+            const int j = gi * GREF + p * S::lanes + pt;
+            const uint32_t o = 4u * (uint32_t)min(j, m - 1);
+            const uint32_t rx = load1(yrs, o, 0), ry = load1(yrs, o, 4 * m);
+            const uint32_t rz = load1(yrs, o, 8 * m);
+            L.x[p] = j < m ? rx - (uint32_t)xofs : kPadRef;      // padding never votes
+            L.yz[p] = j < m ? yz_pack(ry, rz) : yz_pack(kPadRef, kPadRef);
+        }
+        const int lo = __builtin_amdgcn_readlane(w.lo, gi & 63);
+        const int len = __builtin_amdgcn_readlane(w.len, gi & 63);
+        const int i0 = __builtin_amdgcn_readlane(w.i0, gi & 63);
+        const int i1 = __builtin_amdgcn_readlane(w.i1, gi & 63);
+        // whole blocks from the window's first source; what is left after the last of
+        // them belongs to the last part
+        const int nb = len / S::block, full = nb * S::block;
+        const int j0 = lo + (nb * part >> lgp) * S::block;
+        const int j1 = lo + (nb * (part + 1) >> lgp) * S::block;
+        const bool tail = part + 1 == 1 << lgp && full < len;
+        uint32_t tx[S::tail_steps];
+        uint64_t tyz[S::tail_steps];
+        if (tail) {
+#pragma unroll
+            for (int t = 0; t < S::tail_steps; ++t) {
+                const int o = full + S::subs * t + (int)(hoff >> 4);
+                const uint32_t j = (uint32_t)min(lo + o, ns - 1);
+                tx[t] = load1(srs, 4u * j, 0);
+                tyz[t] = ((uint64_t)load1(srs, 8u * j, 4 * ns + 4) << 32) |
+                         (uint64_t)load1(srs, 8u * j, 4 * ns);
+                if (o >= len) {
+                    tx[t] = kPadSrc;
+                    tyz[t] = 0x8000000000000000ull;        // -yz_pack(kPadSrc, kPadSrc)
+                }
+            }
+        }
+        if (j0 < j1) {
+            constexpr int B = S::block;
+            f4u ax, ay, az, bx, by, bz;
+            int j = j0;
+            src_issue_lanes(sdesc, ns, j, hoff, hoff2, ax, ay, az);
+            for (; j + 2 * B <= j1; j += 2 * B) {
+                src_issue_lanes(sdesc, ns, j + B, hoff, hoff2, bx, by, bz);
+                soa_wait<3>(ax, ay, az);
+                if (j >= i0 && j + B <= i1)
+                    vote_block<CW, false>(ax, ay, az, L, v);
+                else
+                    vote_block<CW, true>(ax, ay, az, L, v);
+                src_issue_lanes(sdesc, ns, min(j + 2 * B, j1 - B), hoff, hoff2, ax, ay, az);
+                soa_wait<3>(bx, by, bz);
+                if (j + B >= i0 && j + 2 * B <= i1)
+                    vote_block<CW, false>(bx, by, bz, L, v);
+                else
+                    vote_block<CW, true>(bx, by, bz, L, v);
+            }
+            soa_wait<0>(ax, ay, az);           // the last block issued, used or not
+            if (j + B <= j1) {
+                if (j >= i0 && j + B <= i1)
+                    vote_block<CW, false>(ax, ay, az, L, v);
+                else
+                    vote_block<CW, true>(ax, ay, az, L, v);
+            }
+        }
+        if (tail) {
+#pragma unroll
+            for (int t = 0; t < S::tail_steps; ++t)
+                if (full + S::subs * t < len)
+#pragma unroll
+                    for (int p = 0; p < S::pts; ++p) {
+                        const uint64_t e = add64(L.yz[p], tyz[t]);
+                        vote_pair<CW, false>(L.x[p] - tx[t], (uint32_t)(e >> 32), (uint32_t)e, v);
+                    }
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // asm-issued LDS atomics
+}
+
 // A source's (y, z) pair as the reference's: (y << 32) | (z + 2^31).
 __device__ __forceinline__ uint64_t yz_src(int32_t y, int32_t z)
 {
@@ -774,15 +1039,18 @@ __device__ __forceinline__ uint64_t yz_src(int32_t y, int32_t z)
 // them, so that the vote can restrict each reference lane group to the sources
 // whose pairs can land in the current slab.
 template <int CW>
-__device__ void sort_sources(const SweepArgs &a, const float *R, uint32_t *lds, uint32_t *scr,
-                             int slot)
+__device__ __forceinline__ void sort_sources(const SweepArgs *args, int32_t *sp, int k,
+                                             uint32_t *lds, uint32_t *scr)
 {
+    const SweepArgs a = phase_args(args);
     const Geom &g = a.g;
+    float R[9];
+    load_rotation(a, k, R);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t *cnt = lds;                       // kSrcBuckets counters
     uint32_t *key = lds + kSrcBuckets;         // per source: bucket << 16 | rank
     const int64_t ns = src_stride(a.scratch_stride);
-    int32_t *ox = a.scratch + (size_t)slot * slot_words(a.scratch_stride);
+    int32_t *ox = sp;
     uint64_t *oyz = reinterpret_cast<uint64_t *>(ox + ns);
     int32_t *T = ox + 3 * ns;
     const double S16 = g.S16, Sz = CW == 16 ? g.S15 : g.S16;
@@ -875,78 +1143,54 @@ __device__ void sort_sources(const SweepArgs &a, const float *R, uint32_t *lds, 
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-// Wave64 maximum / minimum of an unsigned value by DPP lane moves (no LDS round
-// trip): pairs and quads by quad permutations, eight and sixteen lanes by the
-// half-row and row mirrors, then row 0 into row 1 and row 2 into row 3
-// (row_bcast:15), rows 0-1 into rows 2-3 (row_bcast:31); lane 63 holds the
-// result, read back as a wave-uniform value.  Lanes a move does not write keep
-// the identity, so inactive sources never change the result.
-template <bool MAX>
-__device__ __forceinline__ uint32_t wave_ext_u32(uint32_t v)
-{
-    const int id = MAX ? 0 : -1;
-    auto op = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0xB1, 0xF, 0xF, false));
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x4E, 0xF, 0xF, false));
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x141, 0xF, 0xF, false));
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x140, 0xF, 0xF, false));
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x142, 0xA, 0xF, false));
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x143, 0xC, 0xF, false));
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return wave_ext_u32<true>(v); }
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return wave_ext_u32<false>(v); }
+// A thread's counters of one slab.
+constexpr int kScanMax = (kHistWordsMax / 4 + kBlock - 1) / kBlock;
+struct SlabWords {
+    uint4 v[kScanMax];
+};
 
-// Largest counter of a slab (words4 uint4 of counters), workgroup-uniform;
-// `mine` receives the largest counter among this thread's own words.
+// Read a slab (words4 uint4 of counters) into registers and clear it for the next one
+// in the same pass over LDS; returns the largest count among this wave's words.  LDS
+// bandwidth bounds it (one read and one write of the slab).
 template <int CW>
-__device__ uint32_t slab_max(const uint32_t *hist, int words4, uint32_t *scr, uint32_t &mine)
+__device__ __forceinline__ uint32_t take_slab(uint32_t *hist, int words4, SlabWords &r)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint4 *h4 = reinterpret_cast<const uint4 *>(hist);
+    const int tid = threadIdx.x;
+    uint4 *h4 = reinterpret_cast<uint4 *>(hist);
+#pragma unroll
+    for (int i = 0; i < kScanMax; ++i) {
+        const int w = tid + i * kBlock;
+        r.v[i] = w < words4 ? h4[w] : make_uint4(0, 0, 0, 0);
+    }
+    u16x2 m16 = {0, 0};
     uint32_t mx = 0;
-    if (CW == 16) {
-        u16x2 m = {0, 0};
-        for (int w = tid; w < words4; w += kBlock) {
-            const uint4 v = h4[w];
-            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v.x));
-            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v.y));
-            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v.z));
-            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v.w));
-        }
-        mx = max((uint32_t)m.x, (uint32_t)m.y);
-    } else {
-        for (int w = tid; w < words4; w += kBlock) {
-            const uint4 v = h4[w];
-            mx = max(mx, max(max(v.x, v.y), max(v.z, v.w)));
+#pragma unroll
+    for (int i = 0; i < kScanMax; ++i) {
+        const int w = tid + i * kBlock;
+        if (w < words4) h4[w] = make_uint4(0, 0, 0, 0);
+        if (CW == 16) {
+            m16 = __builtin_elementwise_max(m16, __builtin_bit_cast(u16x2, r.v[i].x));
+            m16 = __builtin_elementwise_max(m16, __builtin_bit_cast(u16x2, r.v[i].y));
+            m16 = __builtin_elementwise_max(m16, __builtin_bit_cast(u16x2, r.v[i].z));
+            m16 = __builtin_elementwise_max(m16, __builtin_bit_cast(u16x2, r.v[i].w));
+        } else {
+            mx = max(mx, max(max(r.v[i].x, r.v[i].y), max(r.v[i].z, r.v[i].w)));
         }
     }
-    mine = mx;
-    mx = wave_max_u32(mx);
-    if (lane == 0) scr[8 + wave] = mx;
-    __syncthreads();
-    uint32_t r = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) r = max(r, scr[8 + w]);
-    // no closing barrier: every hist read came before the barrier above, and
-    // scr[8..23] is written next by the next slab's scan, two barriers later
-    return r;
+    if (CW == 16) mx = max((uint32_t)m16.x, (uint32_t)m16.y);
+    return wave_max_u32(mx);
 }
 
-// Lowest position (word index * 2 + half for 16-bit counters) whose count is c.
-// Only threads whose own largest counter (`mine` of slab_max) is c can hold it,
-// so the others skip the scan.
+// Lowest position of count c among this wave's words (word index, or twice that + half
+// for 16-bit counters).
 template <int CW>
-__device__ uint32_t slab_first(const uint32_t *hist, int words4, uint32_t c, uint32_t pos0,
-                               uint32_t *scr, uint32_t mine)
+__device__ __forceinline__ uint32_t first_of(const SlabWords &r, uint32_t c)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint4 *h4 = reinterpret_cast<const uint4 *>(hist);
     uint32_t best = 0xFFFFFFFFu;
-    const int wend = mine == c ? words4 : 0;
-    for (int w = tid; w < wend && best == 0xFFFFFFFFu; w += kBlock) {
-        const uint4 v = h4[w];
-        const uint32_t e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = kScanMax - 1; i >= 0; --i) {
+        const uint32_t w = threadIdx.x + (uint32_t)(i * kBlock);
+        const uint32_t e[4] = {r.v[i].x, r.v[i].y, r.v[i].z, r.v[i].w};
 #pragma unroll
         for (int q = 3; q >= 0; --q) {
             if (CW == 16) {
@@ -957,14 +1201,7 @@ __device__ uint32_t slab_first(const uint32_t *hist, int words4, uint32_t c, uin
             }
         }
     }
-    best = wave_min_u32(best);
-    if (lane == 0) scr[24 + wave] = best;
-    __syncthreads();
-    uint32_t r = 0xFFFFFFFFu;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) r = min(r, scr[24 + w]);
-    // no closing barrier (its own scratch words, hist reads before the barrier)
-    return pos0 + r;
+    return wave_min_u32(best);
 }
 
 // Out of line: inlined, the power function's code sits inside every sweep kernel
@@ -1117,10 +1354,13 @@ __device__ __forceinline__ float df_trilinear(const Field &f, float qx, float qy
 // whole workgroup, and write its record.  kScoreNone writes the record unscored
 // (error +inf, 0 inliers).
 template <int SCORER>
-__device__ void score_candidate(const SweepArgs &a, int k, const float *R, int bx, int by, int bz,
-                                uint32_t votes, uint32_t *lds)
+__device__ __forceinline__ void score_candidate(const SweepArgs *args, int k, int bx, int by,
+                                                int bz, uint32_t votes, uint32_t *lds)
 {
+    const SweepArgs a = phase_args(args);
     const Geom &g = a.g;
+    float R[9];
+    load_rotation(a, k, R);
     uint32_t *hist = lds;
     uint32_t *scr = lds + kHistWordsMax;          // kScratchWords words
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1228,108 +1468,140 @@ __device__ void score_candidate(const SweepArgs &a, int k, const float *R, int b
     __syncthreads();                          // LDS scratch reused by the caller
 }
 
-// The vote of one slab with the lane-group size and source layout of this call.
-template <int CW, bool WIDE>
-__device__ __forceinline__ void vote_slab_any(const SweepArgs &a, const float *R, int x0, int np,
-                                              uint32_t *hist, int slot, bool sorted, int lg)
+// The vote of one slab in the general path: planes too wide for the windowed
+// vote's 16-bit strides, or sources too many to be sorted.
+template <int CW>
+__device__ __forceinline__ void vote_slab_any(const SweepArgs *args, int32_t *sp, int k, int x0,
+                                              int np, uint32_t *hist, bool wide)
 {
-    if (!sorted)
-        vote_slab<CW, 6, false, WIDE>(a, R, x0, np, hist, slot);
-    else if (lg == 3)
-        vote_slab<CW, 3, true, WIDE>(a, R, x0, np, hist, slot);
-    else if (lg == 4)
-        vote_slab<CW, 4, true, WIDE>(a, R, x0, np, hist, slot);
-    else
-        vote_slab<CW, 5, true, WIDE>(a, R, x0, np, hist, slot);
+    if (wide) {
+        if (sp)
+            vote_slab<CW, true, true>(args, sp, k, x0, np, hist);
+        else
+            vote_slab<CW, false, true>(args, sp, k, x0, np, hist);
+    } else {
+        vote_slab<CW, false, false>(args, sp, k, x0, np, hist);
+    }
 }
 
-// Vote, mode and score one rotation k with the whole workgroup; `slot` selects
-// the workgroup's source-sort scratch.  Writes a.rec[k].
-template <int CW, int SCORER>
-__device__ void sweep_one(const SweepArgs &a, int k, uint32_t *lds, int slot)
+// Vote, mode and score one rotation k with the whole workgroup; sp is the
+// workgroup's source-sort scratch (null: sources not sorted).  Writes a.rec[k].
+template <int CW, int SCORER, int GREF>
+__device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t *lds, int32_t *sp)
 {
-    const Geom &g = a.g;
     uint32_t *hist = lds;
     uint32_t *scr = lds + kHistWordsMax;          // kScratchWords words
     const int tid = threadIdx.x;
-    const uint32_t Sy = g.size[1];
-    const uint32_t RW = (uint32_t)g.row_words;
-    const bool sorted = a.scratch != nullptr;
-    const int lg = a.lane_group == 16   ? 3
-                   : a.lane_group == 32 ? 4
-                   : a.lane_group == 64 ? 5
-                                        : lane_group_log2(g.m, g.n, g.size[0], a.ref_x_extent,
-                                                          a.vote_parts);
-  {
-    float R[9];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) R[e] = kc(a.rot)[9 * k + e];
-    if (sorted) sort_sources<CW>(a, R, lds, scr, slot);
+    if (GREF || sp) sort_sources<CW>(args, sp, k, lds, scr);
 
     // ---------------- vote + mode over the slabs ----------------
-    // Barriers per slab: after the clear, after the vote, and one inside each
-    // scan (after its per-wave partials); the scans read hist only before theirs,
-    // so the next slab's clear (or the scoring) needs no further barrier.
-    uint32_t best_c = 0, best_p = 0xFFFFFFFFu;
-    for (int slab = 0; slab < g.nslabs; ++slab) {
-        const int x0 = slab * g.pps;
-        const int np = min(g.pps, g.size[0] - x0);
-        const int words = np * (int)Sy * (int)RW;
-        const int words4 = (words + 3) >> 2;
-        uint4 *h4 = reinterpret_cast<uint4 *>(hist);
-        for (int w = tid; w < words4; w += kBlock) h4[w] = make_uint4(0, 0, 0, 0);
+    // Two barriers per slab, after the vote and after the scan.  The scan leaves the slab
+    // cleared and its counters in registers; only the waves that hold a new largest
+    // count look for its position, after the barrier, while the others vote on (a
+    // later slab never wins a tie: its positions are higher).
+    const SweepArgs a = phase_args(args);
+    const Geom &g = a.g;
+    const uint32_t Sy = g.size[1], RW = (uint32_t)g.row_words;
+    uint4 *h4 = reinterpret_cast<uint4 *>(hist);
+    for (int w = tid; w < (g.slab_words + 3) >> 2; w += kBlock) h4[w] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) scr[kUnitCounter] = 0u;
+    __syncthreads();
+    uint32_t best_c = 0, wave_p = 0xFFFFFFFFu;
+    const int size_x = g.size[0], pps = g.pps;
+    const uint32_t plane = Sy * RW;
+    for (int x0 = 0; x0 < size_x; x0 += pps) {
+        const int np = min(pps, size_x - x0);
+        if (GREF)
+            vote_windows<CW, GREF ? GREF : 64>(args, sp, x0, np, hist);
+        else
+            vote_slab_any<CW>(args, sp, k, x0, np, hist, g.wide != 0);
+        __syncthreads();
+        SlabWords words;
+        const uint32_t c = take_slab<CW>(hist, (int)((uint32_t)np * plane + 3) >> 2, words);
+        if ((tid & 63) == 0) scr[8 + (tid >> 6)] = c;
         if (tid == 0) scr[kUnitCounter] = 0u;
         __syncthreads();
-        if (g.wide)
-            vote_slab_any<CW, true>(a, R, x0, np, hist, slot, sorted, lg);
-        else
-            vote_slab_any<CW, false>(a, R, x0, np, hist, slot, sorted, lg);
-        __syncthreads();
-        // the slab's largest count first (cheap), and only when it beats the best of
-        // the earlier slabs its lowest position (a later slab never wins a tie: its
-        // positions are higher)
-        const uint32_t pos0 = (uint32_t)x0 * Sy * RW * (CW == 16 ? 2u : 1u);
-        uint32_t mine;
-        const uint32_t smax = slab_max<CW>(hist, words4, scr, mine);
-        if (smax > best_c) {
-            best_p = slab_first<CW>(hist, words4, smax, pos0, scr, mine);
-            best_c = smax;
+        uint32_t m = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) m = max(m, scr[8 + w]);
+        m = (uint32_t)uni((int)m);
+        if (m > best_c) {
+            best_c = m;
+            wave_p = 0xFFFFFFFFu;
+            if (c == m) wave_p = (uint32_t)x0 * plane * (CW == 16 ? 2u : 1u) + first_of<CW>(words, m);
         }
     }
+    if ((tid & 63) == 0) scr[24 + (tid >> 6)] = wave_p;
+    __syncthreads();
+    uint32_t best_p = 0xFFFFFFFFu;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) best_p = min(best_p, scr[24 + w]);
+    best_p = (uint32_t)uni((int)best_p);
 
-    dses_record rec;
     if (best_c == 0) {
         if (tid == 0) {
+            dses_record rec;
             rec.bin[0] = rec.bin[1] = rec.bin[2] = 0;
             rec.votes = 0;
             rec.inliers = 0;
             rec.error = INFINITY;
-            a.rec[k] = rec;
+            phase_args(args).rec[k] = rec;
         }
         return;
     }
     // position -> box-relative bin
+    const SweepArgs c = phase_args(args);
+    const uint32_t rw = (uint32_t)c.g.row_words, sy = (uint32_t)c.g.size[1];
     const uint32_t w = CW == 16 ? best_p >> 1 : best_p;
-    const uint32_t row = w / RW;
-    const int cz = (int)((w - row * RW) * (CW == 16 ? 2u : 1u) + (CW == 16 ? (best_p & 1u) : 0u));
-    const int cy = (int)(row % Sy), cx = (int)(row / Sy);
-    const int bx = cx + g.klo[0], by = cy + g.klo[1], bz = cz + g.klo[2];
-    score_candidate<SCORER>(a, k, R, bx, by, bz, best_c, lds);
-  }
+    const uint32_t row = w / rw;
+    const int cz = (int)((w - row * rw) * (CW == 16 ? 2u : 1u) + (CW == 16 ? (best_p & 1u) : 0u));
+    const int cy = (int)(row % sy), cx = (int)(row / sy);
+    const int bx = cx + c.g.klo[0], by = cy + c.g.klo[1], bz = cz + c.g.klo[2];
+    score_candidate<SCORER>(args, k, bx, by, bz, best_c, lds);
 }
 
-template <int CW, int SCORER>
+// A kernel's by-value argument as a pointer for phase_args.
+__device__ __forceinline__ const SweepArgs *kernel_args()
+{
+    return (const SweepArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+template <int CW, int SCORER, int GREF>
 __global__ void __launch_bounds__(kBlock) k_sweep(SweepArgs a)
 {
     __shared__ __align__(16) uint32_t lds[kLdsWords];
-    for (int k = blockIdx.x; k < a.k; k += gridDim.x) sweep_one<CW, SCORER>(a, k, lds, blockIdx.x);
+    int32_t *sp = a.scratch ? a.scratch + (size_t)blockIdx.x * slot_words(a.scratch_stride)
+                            : nullptr;
+    for (int k = blockIdx.x; k < a.k; k += gridDim.x)
+        sweep_one<CW, SCORER, GREF>(kernel_args(), k, lds, sp);
 }
 
 template <int CW, int SC>
 static hipError_t launch_one(const SweepArgs &a, int grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((k_sweep<CW, SC>), dim3(grid), dim3(kBlock), 0, stream, a);
+    switch (a.gref) {
+    case 32:
+        hipLaunchKernelGGL((k_sweep<CW, SC, 32>), dim3(grid), dim3(kBlock), 0, stream, a);
+        break;
+    case 64:
+        hipLaunchKernelGGL((k_sweep<CW, SC, 64>), dim3(grid), dim3(kBlock), 0, stream, a);
+        break;
+    default:
+        hipLaunchKernelGGL((k_sweep<CW, SC, 0>), dim3(grid), dim3(kBlock), 0, stream, a);
+    }
     return hipGetLastError();
+}
+
+template <int CW>
+static hipError_t launch_width(const SweepArgs &a, int scorer, int grid, hipStream_t stream)
+{
+    switch (scorer) {
+    case kScoreNone: return launch_one<CW, kScoreNone>(a, grid, stream);
+    case kScoreVotes: return launch_one<CW, kScoreVotes>(a, grid, stream);
+    case DSES_SCORER_BRUTE: return launch_one<CW, DSES_SCORER_BRUTE>(a, grid, stream);
+    case DSES_SCORER_GRID: return launch_one<CW, DSES_SCORER_GRID>(a, grid, stream);
+    default: return launch_one<CW, DSES_SCORER_DF>(a, grid, stream);
+    }
 }
 
 // grid: persistent workgroups (each sweeps rotations blockIdx.x, +gridDim.x, ...);
@@ -1338,22 +1610,8 @@ hipError_t launch_sweep(const SweepArgs &a, int scorer, int grid, hipStream_t st
 {
     if (a.k <= 0) return hipSuccess;
     if (grid > a.k) grid = a.k;
-    if (a.g.counter_bits == 16) {
-        switch (scorer) {
-        case kScoreNone: return launch_one<16, kScoreNone>(a, grid, stream);
-        case kScoreVotes: return launch_one<16, kScoreVotes>(a, grid, stream);
-        case DSES_SCORER_BRUTE: return launch_one<16, DSES_SCORER_BRUTE>(a, grid, stream);
-        case DSES_SCORER_GRID: return launch_one<16, DSES_SCORER_GRID>(a, grid, stream);
-        default: return launch_one<16, DSES_SCORER_DF>(a, grid, stream);
-        }
-    }
-    switch (scorer) {
-    case kScoreNone: return launch_one<32, kScoreNone>(a, grid, stream);
-    case kScoreVotes: return launch_one<32, kScoreVotes>(a, grid, stream);
-    case DSES_SCORER_BRUTE: return launch_one<32, DSES_SCORER_BRUTE>(a, grid, stream);
-    case DSES_SCORER_GRID: return launch_one<32, DSES_SCORER_GRID>(a, grid, stream);
-    default: return launch_one<32, DSES_SCORER_DF>(a, grid, stream);
-    }
+    return a.g.counter_bits == 16 ? launch_width<16>(a, scorer, grid, stream)
+                                  : launch_width<32>(a, scorer, grid, stream);
 }
 
 // --------------------------------------------------------------------------
@@ -1402,10 +1660,7 @@ __global__ void __launch_bounds__(kBlock) k_score_pruned(SweepArgs a, float q,
         for (int k = k0; k < k1; ++k) {
             const dses_record r = a.rec[k];
             if (!keep_candidate(r.votes, ms, q)) continue;
-            float R[9];
-#pragma unroll
-            for (int e = 0; e < 9; ++e) R[e] = kc(a.rot)[9 * k + e];
-            score_candidate<SCORER>(a, k, R, r.bin[0], r.bin[1], r.bin[2], r.votes, lds);
+            score_candidate<SCORER>(kernel_args(), k, r.bin[0], r.bin[1], r.bin[2], r.votes, lds);
         }
     }
 }
@@ -1754,49 +2009,77 @@ __device__ void finish_item(const BatchArgs &b, const BatchItem &w, const SweepA
     __syncthreads();
 }
 
-template <int SCORER>
+// One item of a batched launch: rotations [k0, k1) of one instance.
+template <int CW, int SCORER, int GREF>
+__device__ __forceinline__ void sweep_item(const SweepArgs *args, const BatchItem &w, uint32_t *lds,
+                                           int32_t *sp)
+{
+    for (int k = w.k0; k < w.k1; ++k) sweep_one<CW, SCORER, GREF>(args, k, lds, sp);
+}
+
+// GENERAL: the items of instances that only the general path can run, header[0] ..
+// header[2] of the list, taken by a launch of their own (so that the windowed
+// vote's kernel holds no other code); else items 0 .. header[0].
+template <int SCORER, bool GENERAL>
 __global__ void __launch_bounds__(kBlock) k_sweep_batch(BatchArgs b)
 {
     __shared__ __align__(16) uint32_t lds[kLdsWords];
-    const int n_items = __builtin_amdgcn_readfirstlane(*(kint)(const int32_t *)b.header);
+    const kint header = kc(b.header);
+    const int first = GENERAL ? header[0] : 0;
+    const int n_items = GENERAL ? header[2] - first : header[0];
     for (;;) {
         if (threadIdx.x == 0) lds[kLdsWords - 1] = atomicAdd(b.cursor, 1u) - b.cursor_base;
         __syncthreads();
         const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds[kLdsWords - 1]);
         __syncthreads();
         if (it >= (uint32_t)n_items) break;
-        const BatchItem w = kload(b.items + it);
-        SweepArgs a = kload(b.inst + w.inst);
-        int slot = blockIdx.x;
-        if (b.scratch && a.scratch) {
-            // this launch's slot; the instance's own stride lays out the arrays in it
-            a.scratch = b.scratch + (size_t)blockIdx.x * (size_t)b.scratch_slot;
-            slot = 0;
-        }
-        for (int k = w.k0; k < w.k1; ++k) {
-            if (a.g.counter_bits == 16)
-                sweep_one<16, SCORER>(a, k, lds, slot);
+        const BatchItem w = kload(b.items + first + it);
+        const SweepArgs *args = b.inst + w.inst;
+        const SweepArgs a = phase_args(args);
+        int32_t *sp = nullptr;
+        if (a.scratch)   // this launch's slot (the instance's own stride lays out the arrays in it)
+            sp = b.scratch ? b.scratch + (size_t)blockIdx.x * (size_t)b.scratch_slot
+                           : a.scratch + (size_t)blockIdx.x * slot_words(a.scratch_stride);
+        const bool c16 = a.g.counter_bits == 16;
+        if (GENERAL) {
+            if (c16)
+                sweep_item<16, SCORER, 0>(args, w, lds, sp);
             else
-                sweep_one<32, SCORER>(a, k, lds, slot);
+                sweep_item<32, SCORER, 0>(args, w, lds, sp);
+        } else if (!c16) {
+            sweep_item<32, SCORER, 64>(args, w, lds, sp);
+        } else if (a.gref == 64) {
+            sweep_item<16, SCORER, 64>(args, w, lds, sp);
+        } else {
+            sweep_item<16, SCORER, 32>(args, w, lds, sp);
         }
-        if (b.done_rot) finish_item(b, w, a, lds);
+        if (b.done_rot) finish_item(b, w, phase_args(args), lds);
     }
 }
 
-hipError_t launch_sweep_batch(const BatchArgs &b, int scorer, int grid, hipStream_t stream)
+template <bool GENERAL>
+static hipError_t launch_batch_kind(const BatchArgs &b, int scorer, int grid, hipStream_t stream)
 {
+    const dim3 g(grid), t(kBlock);
     switch (scorer) {
     case DSES_SCORER_BRUTE:
-        hipLaunchKernelGGL(k_sweep_batch<DSES_SCORER_BRUTE>, dim3(grid), dim3(kBlock), 0, stream, b);
+        hipLaunchKernelGGL((k_sweep_batch<DSES_SCORER_BRUTE, GENERAL>), g, t, 0, stream, b);
         break;
     case DSES_SCORER_GRID:
-        hipLaunchKernelGGL(k_sweep_batch<DSES_SCORER_GRID>, dim3(grid), dim3(kBlock), 0, stream, b);
+        hipLaunchKernelGGL((k_sweep_batch<DSES_SCORER_GRID, GENERAL>), g, t, 0, stream, b);
         break;
     default:
-        hipLaunchKernelGGL(k_sweep_batch<DSES_SCORER_DF>, dim3(grid), dim3(kBlock), 0, stream, b);
+        hipLaunchKernelGGL((k_sweep_batch<DSES_SCORER_DF, GENERAL>), g, t, 0, stream, b);
         break;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_sweep_batch(const BatchArgs &b, int scorer, bool general, int grid,
+                              hipStream_t stream)
+{
+    return general ? launch_batch_kind<true>(b, scorer, grid, stream)
+                   : launch_batch_kind<false>(b, scorer, grid, stream);
 }
 
 __global__ void k_stage_batch(const StageDesc *d, const int32_t *header)
@@ -1805,8 +2088,7 @@ __global__ void k_stage_batch(const StageDesc *d, const int32_t *header)
     for (int inst = blockIdx.y; inst < count; inst += gridDim.y) {
         const StageDesc sd = d[inst];
         for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < sd.m; j += gridDim.x * blockDim.x)
-            stage_point(sd.tgt, sd.perm ? sd.perm[j] : j, j, sd.m, sd.S16, sd.S15, sd.klo, sd.yq,
-                        sd.yt);
+            stage_point(sd, j);
     }
 }
 

@@ -76,13 +76,21 @@ int64_t target_block_population(TargetRes *tm, const Params &p)
     return e.pop;
 }
 
-dses_status ensure_target_stage(TargetRes *tm, const Params &p, hipStream_t stream,
-                                const TargetRes::Stage **out)
+bool target_x_range(TargetRes *tm, const Params &p, int32_t *ylo, int32_t *yhi)
 {
     std::lock_guard<std::mutex> gl(tm->grid_mu);
+    if (tm->perm_x.empty()) sort_by_x(tm->host_aos.data(), tm->m, &tm->perm_x);
+    return ref_x_range(tm->host_aos.data(), tm->perm_x, p.delta, p.klo[0], ylo, yhi);
+}
+
+dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, int gref,
+                                hipStream_t stream, const TargetRes::Stage **out)
+{
+    std::lock_guard<std::mutex> gl(tm->grid_mu);
+    const StageDesc want = stage_desc(g, gref, nullptr, nullptr, nullptr, nullptr);
     for (const auto &st : tm->stages)
         if (st.delta == p.delta && st.klo[0] == p.klo[0] && st.klo[1] == p.klo[1] &&
-            st.klo[2] == p.klo[2]) {
+            st.klo[2] == p.klo[2] && st.zbits == want.zbits && st.gref == gref) {
             *out = &st;
             return DSES_OK;
         }
@@ -98,14 +106,13 @@ dses_status ensure_target_stage(TargetRes *tm, const Params &p, hipStream_t stre
         }
         tm->d_perm = perm;
     }
-    double S16, S15;
-    lattice_scales(p.delta, &S16, &S15);
-    TargetRes::Stage st{p.delta, {p.klo[0], p.klo[1], p.klo[2]}, nullptr, nullptr, false, 0, 0};
-    st.sorted = ref_x_range(tm->host_aos.data(), tm->perm_x, p.delta, p.klo[0], &st.ylo, &st.yhi);
-    hipError_t e = dev_alloc(&st.yq, 16 * m);
+    TargetRes::Stage st{p.delta, {p.klo[0], p.klo[1], p.klo[2]}, want.zbits, gref,
+                        nullptr, nullptr};
+    hipError_t e = dev_alloc(&st.yq, 4 * stage_words(m));
     if (e == hipSuccess) e = dev_alloc(&st.yt, 12 * m);
     if (e == hipSuccess)
-        e = launch_stage(tm->aos, tm->d_perm, tm->m, S16, S15, p.klo, st.yq, st.yt, stream);
+        e = launch_stage(stage_desc(g, gref, tm->aos, tm->d_perm, st.yq, st.yt),
+                         stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {
         if (st.yq) (void)hipFree(st.yq);

@@ -90,6 +90,7 @@ struct Request {
     const RotRes *rots = nullptr;
     std::vector<float> src;
     int32_t n = 0, m = 0, k = 0;
+    bool general = false;                    // needs the sweep's general path
     Params p{};
     int scorer = DSES_SCORER_GRID;
     // lifecycle
@@ -325,7 +326,10 @@ dses_status ServerImpl::prepare(Request *r)
     dses_status st = plan_geom(c, r->p, r->n, r->m, bits, &g);
     if (st != DSES_OK) return st;
     const TargetRes::Stage *stg = nullptr;
-    if ((st = ensure_target_stage(tm, r->p, up, &stg)) != DSES_OK) return st;
+    int32_t ylo = 0, yhi = 0;
+    const bool sorted = r->n <= kSortMax && target_x_range(tm, r->p, &ylo, &yhi);
+    const int gref = choose_batch_gref(g, sorted, ref_x_extent(ylo, yhi));
+    if ((st = ensure_target_stage(tm, r->p, g, gref, up, &stg)) != DSES_OK) return st;
     CellGrid cg{};
     if (r->scorer == DSES_SCORER_GRID && (st = ensure_target_grid(tm, r->p.r, &cg)) != DSES_OK)
         return st;
@@ -348,11 +352,11 @@ dses_status ServerImpl::prepare(Request *r)
     a.rot = r->rots->rot;
     a.yq = stg->yq;
     a.yt = stg->yt;
-    const bool sorted = r->n <= kSortMax && stg->sorted;
     a.scratch = sorted ? reinterpret_cast<int32_t *>(4) : nullptr;   // per-slice scratch at launch
     a.scratch_stride = r->n;                 // arrays inside the slice's fixed-size slots
-    source_buckets(stg->ylo, stg->yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-    a.ref_x_extent = ref_x_extent(stg->ylo, stg->yhi);
+    source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
+    a.gref = gref;
+    r->general = gref == 0;
     a.g = g;
     a.grid = cg;
     if (r->scorer == DSES_SCORER_DF) {
@@ -425,13 +429,14 @@ bool ServerImpl::launch_slice()
     std::stable_sort(order.begin(), order.end(),
                      [&](const Request *a, const Request *b) { return prio(a) < prio(b); });
     const int scorer = order.front()->scorer;      // one kernel instantiation per slice
+    const bool general = order.front()->general;
     int n_items = 0;
     double budget = slice_pairs;
     s->n_last = 0;
     s->carried.clear();
     for (Request *r : order) {
         if (budget <= 0.0 || n_items >= kMaxSliceItems) break;
-        if (r->scorer != scorer) continue;
+        if (r->scorer != scorer || r->general != general) continue;
         const double per_tile_target = std::max(1.0, slice_pairs / (4.0 * grid));
         const int32_t tile =
             (int32_t)std::max(1.0, std::min((double)r->k, per_tile_target / r->pair_cost));
@@ -445,8 +450,9 @@ bool ServerImpl::launch_slice()
         }
         if (r->next_k == r->k) ++s->n_last;
     }
-    s->h_header[0] = n_items;
+    s->h_header[0] = general ? 0 : n_items;
     s->h_header[1] = 0;
+    s->h_header[2] = n_items;
     s->pairs = slice_pairs - budget;
     s->t_launch = Clock::now();
     mu.unlock();
@@ -459,7 +465,7 @@ bool ServerImpl::launch_slice()
     roctxMarkA("dses.slice_launch");
     BatchArgs ba{d_args, s->dv_items, s->dv_header, s->d_cursor, s->d_scratch,
                  slot_words(kServeMaxSrc), s->cursor, d_done, dv_res, dv_flag};
-    chk(launch_sweep_batch(ba, scorer, grid, st));
+    chk(launch_sweep_batch(ba, scorer, general, grid, st));
     chk(hipEventRecord(s->swept, st));
     s->cursor += (uint32_t)(n_items + grid);   // every workgroup fetches once past the end
     ++n_slices;
