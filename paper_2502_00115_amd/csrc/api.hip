@@ -267,11 +267,12 @@ int choose_gref(const Geom &g, bool sorted, float x_extent, int asked)
     return 64.0f * x_extent <= 0.13f * (float)g.pps * (float)g.m ? 64 : 32;
 }
 
-StageDesc stage_desc(const Geom &g, int gref, const float *tgt, const int32_t *perm, int32_t *yq,
-                     float *yt)
+StageDesc stage_desc(const Geom &g, int gref, bool arrange, const float *tgt, const int32_t *perm,
+                     int32_t *yq, float *yt)
 {
     return StageDesc{tgt,     perm, g.m,  g.S16, g.S15, {g.klo[0], g.klo[1], g.klo[2]},
-                     g.zbits, gref ? gref : 64, yq, yt};
+                     g.zbits, gref ? gref : 64, arrange ? 1 : 0,
+                     g.row_words * g.size[1], g.row_words, yq, yt};
 }
 
 // Largest vote count any bin can reach: for a fixed source point the pairs that
@@ -754,7 +755,8 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
                      ref_coord_limit(p), bad};
         DSES_HIP(launch_check(ca, stream));
     }
-    DSES_HIP(launch_stage(stage_desc(g, a.gref, job.tgt, static_cast<int32_t *>(d_perm),
+    const bool arrange = worth_arranging(g, a.gref, ref_x_extent(ylo, yhi), job.k);
+    DSES_HIP(launch_stage(stage_desc(g, a.gref, arrange, job.tgt, static_cast<int32_t *>(d_perm),
                                      static_cast<int32_t *>(d_yq), static_cast<float *>(d_yt)),
                           stream));
     rec_ev(1);

@@ -553,7 +553,8 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                 a.field.inv[q] = x.target->df_inv[q];
             }
         }
-        sd = stage_desc(x.g, a.gref, x.tgt, perm_dev, const_cast<int32_t *>(a.yq), const_cast<float *>(a.yt));
+        sd = stage_desc(x.g, a.gref,
+                        worth_arranging(x.g, a.gref, ref_x_extent(x.ylo, x.yhi), x.k), x.tgt, perm_dev, const_cast<int32_t *>(a.yq), const_cast<float *>(a.yt));
         sl = SelectDesc{a.rec, x.k, x.p.delta, x.rot, res_dev + i, status_dev + i};
     }
     int32_t header[3] = {n_items - n_general, count, n_items};

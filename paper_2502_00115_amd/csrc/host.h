@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <deque>
 #include <cstdint>
@@ -154,9 +155,23 @@ inline int choose_batch_gref(const Geom &g, bool sorted, float x_extent)
     return gref != 0 && g.counter_bits == 32 ? 64 : gref;
 }
 // Staging of a reference of g.m points for a vote of geometry g with lane groups of
-// gref points (0: the general path).
-StageDesc stage_desc(const Geom &g, int gref, const float *tgt, const int32_t *perm,
+// gref points (0: the general path), in bank order if `arrange`.
+StageDesc stage_desc(const Geom &g, int gref, bool arrange, const float *tgt, const int32_t *perm,
                      int32_t *yq, float *yt);
+// Whether a call of k rotations gains from bank order (k_arrange takes 20 us for
+// groups of 32 points, 40 us for 64).  It shortens the LDS accesses of the votes that
+// land in the box, about n m k times the product of size / (2 extent) over the axes
+// for clouds of the reference's extent; 1,203 x 3,001 points and 4,608 rotations
+// (6 10^9 of them) gained 0.23 ms of 4.75.  Groups of 32 points under 16-bit counters
+// (717 x 1,024 points) issue too many other instructions to gain.
+inline bool worth_arranging(const Geom &g, int gref, float x_extent, int64_t k)
+{
+    if (gref == 0 || (gref == 32 && g.counter_bits == 16)) return false;
+    double votes = (double)g.n * g.m * (double)k;
+    for (int a = 0; a < 3; ++a)
+        votes *= std::min(1.0, g.size[a] / (2.0 * (double)x_extent));
+    return votes >= 2.5e9;
+}
 // Upper bound on any bin's vote count (decides 16- vs 32-bit LDS counters):
 // n x the largest reference population of a 2 x 2 x 2 block of cells of pitch
 // slightly above delta (for a fixed source point, the pairs sharing a bin have
@@ -212,7 +227,7 @@ struct TargetRes {
     struct Stage {                           // staged copy for one (delta, box)
         float delta;
         int32_t klo[3];
-        int32_t zbits, gref;                 // the layout it is staged for
+        int32_t zbits, gref, px, py;         // the layout it is staged for
         int32_t *yq;                         // fixed-point copy (stage_words(m) int32)
         float *yt;
     };

@@ -98,8 +98,9 @@ constexpr int kExhaustiveMaxSrc = 12288;
 struct SweepArgs {
     const float *src;      // n x 3 AoS
     const float *rot;      // K x 9
-    const int32_t *yq;     // fixed-point reference (lattice offset folded in), sorted by x: x, y,
-                           // z arrays of m, then the x range of each lane group
+    const int32_t *yq;     // fixed-point reference (lattice offset folded in), sorted by x (in
+                           // lane groups: bank order inside a group): x, y, z arrays of m,
+                           // then the x range of each lane group
     const float *yt;       // reference, SoA (3 * m), same order
     int32_t *scratch;      // per workgroup slot: the rotation's sources sorted by x (below)
     int64_t scratch_stride;   // sources a slot holds (>= n)
@@ -162,6 +163,8 @@ struct StageDesc {
     int32_t klo[3];
     int32_t zbits;         // fraction bits of the staged z
     int32_t gref;          // points per lane group (64 in the general path)
+    int32_t arrange;       // order the points of each group by LDS bank
+    int32_t px, py;        // words per x plane and per z row
     int32_t *yq;           // stage_words(m) int32
     float *yt;
 };

@@ -87,10 +87,11 @@ dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, i
                                 hipStream_t stream, const TargetRes::Stage **out)
 {
     std::lock_guard<std::mutex> gl(tm->grid_mu);
-    const StageDesc want = stage_desc(g, gref, nullptr, nullptr, nullptr, nullptr);
+    const StageDesc want = stage_desc(g, gref, gref != 0, nullptr, nullptr, nullptr, nullptr);
     for (const auto &st : tm->stages)
         if (st.delta == p.delta && st.klo[0] == p.klo[0] && st.klo[1] == p.klo[1] &&
-            st.klo[2] == p.klo[2] && st.zbits == want.zbits && st.gref == gref) {
+            st.klo[2] == p.klo[2] && st.zbits == want.zbits && st.gref == gref &&
+            st.px == want.px && st.py == want.py) {
             *out = &st;
             return DSES_OK;
         }
@@ -106,12 +107,12 @@ dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, i
         }
         tm->d_perm = perm;
     }
-    TargetRes::Stage st{p.delta, {p.klo[0], p.klo[1], p.klo[2]}, want.zbits, gref,
-                        nullptr, nullptr};
+    TargetRes::Stage st{p.delta, {p.klo[0], p.klo[1], p.klo[2]}, want.zbits, gref, want.px,
+                        want.py, nullptr, nullptr};
     hipError_t e = dev_alloc(&st.yq, 4 * stage_words(m));
     if (e == hipSuccess) e = dev_alloc(&st.yt, 12 * m);
     if (e == hipSuccess)
-        e = launch_stage(stage_desc(g, gref, tm->aos, tm->d_perm, st.yq, st.yt),
+        e = launch_stage(stage_desc(g, gref, gref != 0, tm->aos, tm->d_perm, st.yq, st.yt),
                          stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {

@@ -81,3 +81,17 @@ def test_batch_mixes_the_general_path_with_the_windowed_one():
     assert st == [0, 0]
     for a, b in zip(alone[::2], got):
         assert a.records.tobytes() == b.records.tobytes()
+
+
+@pytest.mark.parametrize("n,m,eps,k,lg", [(1100, 2500, 0.03, 2304, 64), (2600, 4097, 0.03, 640, 32),
+                                          (2600, 8200, 0.03, 320, 64)])
+def test_bank_order_does_not_change_records(n, m, eps, k, lg):
+    """Calls long enough for the staging to order each lane group's points by LDS bank
+    (a last group that is not full keeps its order): every record equals that of a
+    call of few rotations, which keeps the points in x order."""
+    src, tgt, _ = _clouds(n, m, 9)
+    rot = synth.random_rotations(np.random.default_rng(1), k).reshape(-1, 9).astype(np.float32)
+    got = dses.register(src, tgt, rot, eps, records=True, lane_group=lg)
+    for lo in range(0, k, k // 4):
+        part = dses.register(src, tgt, rot[lo:lo + 16], eps, records=True, lane_group=lg)
+        assert part.records.tobytes() == got.records[lo:lo + 16].tobytes()
