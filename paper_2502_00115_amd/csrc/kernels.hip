@@ -1831,6 +1831,40 @@ __device__ __forceinline__ bool exh_better(float e, int i, uint32_t u, float oe,
     return ou < u;
 }
 
+// The workgroup's best translation of rotation k into its record.
+__device__ __forceinline__ void exh_record(const SweepArgs &a, int k, float be, int bi, uint32_t bu,
+                                           float *re, int *ri, uint32_t *ru)
+{
+    const Geom &g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t sz = (uint32_t)g.size[2], syz = (uint32_t)g.size[1] * sz;
+    for (int off = 32; off > 0; off >>= 1) {
+        const float oe = __shfl_xor(be, off, 64);
+        const int oi = __shfl_xor(bi, off, 64);
+        const uint32_t ou = (uint32_t)__shfl_xor((int)bu, off, 64);
+        if (exh_better(be, bi, bu, oe, oi, ou)) { be = oe; bi = oi; bu = ou; }
+    }
+    if (lane == 0) { re[wave] = be; ri[wave] = bi; ru[wave] = bu; }
+    __syncthreads();
+    if (tid == 0) {
+        float e = re[0];
+        int c = ri[0];
+        uint32_t w = ru[0];
+        for (int q = 1; q < kWaves; ++q)
+            if (exh_better(e, c, w, re[q], ri[q], ru[q])) { e = re[q]; c = ri[q]; w = ru[q]; }
+        const uint32_t ux = w / syz, uy = (w - ux * syz) / sz, uz = w - ux * syz - uy * sz;
+        dses_record rec;
+        rec.bin[0] = g.klo[0] + (int)ux;
+        rec.bin[1] = g.klo[1] + (int)uy;
+        rec.bin[2] = g.klo[2] + (int)uz;
+        rec.votes = 1u;
+        rec.inliers = c;
+        rec.error = e;
+        a.rec[k] = rec;
+    }
+    __syncthreads();                           // the reduction slots are reused
+}
+
 template <int SCORER>
 __global__ void __launch_bounds__(kBlock) k_exhaustive(SweepArgs a)
 {
@@ -1839,7 +1873,7 @@ __global__ void __launch_bounds__(kBlock) k_exhaustive(SweepArgs a)
     __shared__ int ri[kWaves];
     __shared__ uint32_t ru[kWaves];
     const Geom &g = a.g;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     const int n = g.n;
     const uint32_t sz = (uint32_t)g.size[2], syz = (uint32_t)g.size[1] * sz;
     const uint32_t T = (uint32_t)g.size[0] * syz;
@@ -1875,32 +1909,221 @@ __global__ void __launch_bounds__(kBlock) k_exhaustive(SweepArgs a)
             }
             if (exh_better(be, bi, bu, err, inl, u)) { be = err; bi = inl; bu = u; }
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            const float oe = __shfl_xor(be, off, 64);
-            const int oi = __shfl_xor(bi, off, 64);
-            const uint32_t ou = (uint32_t)__shfl_xor((int)bu, off, 64);
-            if (exh_better(be, bi, bu, oe, oi, ou)) { be = oe; bi = oi; bu = ou; }
-        }
-        if (lane == 0) { re[wave] = be; ri[wave] = bi; ru[wave] = bu; }
-        __syncthreads();
-        if (tid == 0) {
-            float e = re[0];
-            int c = ri[0];
-            uint32_t w = ru[0];
-            for (int q = 1; q < kWaves; ++q)
-                if (exh_better(e, c, w, re[q], ri[q], ru[q])) { e = re[q]; c = ri[q]; w = ru[q]; }
-            const uint32_t ux = w / syz, uy = (w - ux * syz) / sz, uz = w - ux * syz - uy * sz;
-            dses_record rec;
-            rec.bin[0] = g.klo[0] + (int)ux;
-            rec.bin[1] = g.klo[1] + (int)uy;
-            rec.bin[2] = g.klo[2] + (int)uz;
-            rec.votes = 1u;
-            rec.inliers = c;
-            rec.error = e;
-            a.rec[k] = rec;
-        }
-        __syncthreads();                       // sp and the reduction slots are reused
+        exh_record(a, k, be, bi, bu, re, ri, ru);
     }
+}
+
+// --------------------------------------------------------------------------
+// The same search from the pairs' side.  Only reference points within r = max(eps,
+// tau) of a query change its term, and the translations that bring source point i
+// within r of reference point j are the few lattice points within r of y_j - R x_i
+// (about 4 of them at r = delta).  So instead of asking for the nearest reference
+// point of every (translation, source point) -- nine rows of the cell grid each -- a
+// workgroup takes the source points a few at a time and lets every reference point
+// lower the distance of its few translations in an LDS array (atomic minimum of the
+// distance's bits), then adds every translation's terms.  The distances are the ones
+// the query form computes and the sums run in the same order, so the records are
+// equal bit for bit.
+//
+// LDS holds kExhRange translations for four source points at a time (two with the L1
+// distance, which takes a second array), so that 256 reference points busy all 16
+// waves and four points share two barriers; longer boxes are taken in ranges, whose
+// reachable reference points are a contiguous run of the x-sorted reference found by
+// bisection.  Bound by vector instructions, about as many in the scatter as in the
+// sum.  64 x 256 points, 577 rotations, 21^3 translations: 2.73 ms with queries,
+// 0.39 ms here.
+// --------------------------------------------------------------------------
+constexpr int kExhRange = 9472;                  // translations per range, a multiple of 4
+constexpr int kExhOwn = (kExhRange / 4 + kBlock - 1) / kBlock;   // uint4 per thread
+enum ExhKind { kExhDist, kExhSquare, kExhL1 };   // what LDS holds: d, d^2, d and L1
+
+template <int KIND>
+__global__ void __launch_bounds__(kBlock) k_exhaustive_scatter(SweepArgs a)
+{
+    constexpr int PB = KIND == kExhL1 ? 2 : 4;       // source points at a time
+    __shared__ __align__(16) uint32_t sd[4 * kExhRange];
+    __shared__ float re[kWaves];
+    __shared__ int ri[kWaves];
+    __shared__ uint32_t ru[kWaves];
+    uint32_t *const sl = sd + 2 * kExhRange;         // kExhL1: L1 distances
+    const Geom &g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int n = g.n, m = g.m;
+    const int Sx = g.size[0], Sy = g.size[1], Sz = g.size[2];
+    const uint32_t syz = (uint32_t)Sy * (uint32_t)Sz, T = (uint32_t)Sx * syz;
+    const float *gx = a.yt, *gy = a.yt + m, *gz = a.yt + 2 * (size_t)m;
+    // a translation within r of y - p has its bin within r / delta of (y - p) / delta;
+    // the slack is more than the float rounding of both sides (every coordinate that
+    // matters is below 2^14 bins, so each of their five roundings is below 1e-3 bins)
+    const float rb = g.r / g.delta, rs = rb + (4e-3f + 1e-5f * rb);
+    const float keep = g.r * g.r * 1.0001f;
+    const float inv = 1.0f / g.delta;
+    // inlier: d < eps, or with squares d^2 < the least square whose root is not below eps
+    float lim = g.eps;
+    if (KIND == kExhSquare) {
+        lim = g.eps * g.eps;
+        while (sqrtf(lim) < g.eps) lim = __uint_as_float(__float_as_uint(lim) + 1u);
+        while (lim > 0.0f && sqrtf(__uint_as_float(__float_as_uint(lim) - 1u)) >= g.eps)
+            lim = __uint_as_float(__float_as_uint(lim) - 1u);
+    }
+    const uint32_t limbits = __float_as_uint(lim);
+    const uint4 far4 = make_uint4(0x7F800000u, 0x7F800000u, 0x7F800000u, 0x7F800000u);
+    for (int q = tid; q < kExhRange; q += kBlock) reinterpret_cast<uint4 *>(sd)[q] = far4;
+    for (int k = blockIdx.x; k < a.k; k += gridDim.x) {
+        float R[9];
+        load_rotation(a, k, R);
+        float be = INFINITY;
+        int bi = 0;
+        uint32_t bu = 0xFFFFFFFFu;
+        for (uint32_t u0 = 0; u0 < T; u0 += kExhRange) {
+            const uint32_t count = min((uint32_t)kExhRange, T - u0);
+            float err[4 * kExhOwn];
+            uint32_t inl[4 * kExhOwn];
+#pragma unroll
+            for (int q = 0; q < 4 * kExhOwn; ++q) {
+                err[q] = 0.0f;
+                inl[q] = 0u;
+            }
+            // the range's first and last x plane
+            const int xa = (int)(u0 / syz), xb = (int)((u0 + count - 1) / syz);
+            const float ta = __fmul_rn((float)(g.klo[0] + xa), g.delta);
+            const float tb = __fmul_rn((float)(g.klo[0] + xb), g.delta);
+            __syncthreads();
+            for (int i0 = 0; i0 < n; i0 += PB) {
+                const int np = min(PB, n - i0);
+                int j0 = 0, mr = m;
+                if (count < T) {
+                    // lane 2 p + e searches end e of source point p's reach
+                    const int i = i0 + min((lane >> 1) & (PB - 1), np - 1);
+                    const float px = fmaf(R[2], a.src[3 * (size_t)i + 2],
+                                          fmaf(R[1], a.src[3 * (size_t)i + 1],
+                                               __fmul_rn(R[0], a.src[3 * (size_t)i])));
+                    const float w = g.r * 1.001f + 1e-6f * (fabsf(px) + fabsf(ta) + fabsf(tb));
+                    const float v = (lane & 1) ? px + tb + w : px + ta - w;
+                    int lo = 0, hi = m;                    // first point not below v
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (gx[mid] < v)
+                            lo = mid + 1;
+                        else
+                            hi = mid;
+                    }
+                    int last = 0;
+                    j0 = m;
+#pragma unroll
+                    for (int p = 0; p < PB; ++p) {
+                        j0 = min(j0, __builtin_amdgcn_readlane(lo, 2 * p));
+                        last = max(last, __builtin_amdgcn_readlane(lo, 2 * p + 1));
+                    }
+                    mr = max(last - j0, 0);
+                }
+                // tasks (source point, reference point), whole waves of reference points
+                const int mw = (mr + 63) & ~63;
+                int p = 0, base = 0;                       // this wave's task is jj of point p
+                for (int t = uni(tid & ~63); t < mw * np; t += kBlock) {
+                    while (t - base >= mw) {
+                        base += mw;
+                        ++p;
+                    }
+                    const int jj = t - base + lane;
+                    if (jj >= mr) continue;
+                    const kfloat x = kc(a.src) + 3 * (size_t)(i0 + p);
+                    float px, py, pz;
+                    rotate(R, x[0], x[1], x[2], px, py, pz);
+                    const float vx = gx[j0 + jj], vy = gy[j0 + jj], vz = gz[j0 + jj];
+                    const float cx = (vx - px) * inv, cy = (vy - py) * inv, cz = (vz - pz) * inv;
+                    const int x0 = max((int)ceilf(cx - rs) - g.klo[0], 0);
+                    const int x1 = min((int)floorf(cx + rs) - g.klo[0], Sx - 1);
+                    const int y0 = max((int)ceilf(cy - rs) - g.klo[1], 0);
+                    const int y1 = min((int)floorf(cy + rs) - g.klo[1], Sy - 1);
+                    const int z0 = max((int)ceilf(cz - rs) - g.klo[2], 0);
+                    const int z1 = min((int)floorf(cz + rs) - g.klo[2], Sz - 1);
+                    uint32_t *const dist = sd + p * kExhRange;
+                    for (int ux = x0; ux <= x1; ++ux) {
+                        const float dx = px + __fmul_rn((float)(ux + g.klo[0]), g.delta) - vx;
+                        const float dx2 = __fmul_rn(dx, dx);
+                        for (int uy = y0; uy <= y1; ++uy) {
+                            const float dy = py + __fmul_rn((float)(uy + g.klo[1]), g.delta) - vy;
+                            const float dxy = fmaf(dy, dy, dx2);
+                            if (dxy > keep) continue;
+                            const uint32_t row =
+                                (uint32_t)ux * syz + (uint32_t)uy * (uint32_t)Sz - u0;
+                            for (int uz = z0; uz <= z1; ++uz) {
+                                const uint32_t at = row + (uint32_t)uz;
+                                const float dz =
+                                    pz + __fmul_rn((float)(uz + g.klo[2]), g.delta) - vz;
+                                const float d2 = fmaf(dz, dz, dxy);
+                                if (at >= count || d2 > keep) continue;
+                                atomicMin(&dist[at],
+                                          __float_as_uint(KIND == kExhSquare ? d2 : sqrtf(d2)));
+                                if (KIND == kExhL1)
+                                    atomicMin(&sl[p * kExhRange + at],
+                                              __float_as_uint(fabsf(dx) + fabsf(dy) + fabsf(dz)));
+                            }
+                        }
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < kExhOwn; ++q) {
+                    const int v4 = tid + q * kBlock;
+                    if (4 * v4 < (int)count) {
+                        for (int pp = 0; pp < np; ++pp) {
+                            uint4 *const d4 = reinterpret_cast<uint4 *>(sd + pp * kExhRange) + v4;
+                            const uint4 d = *d4;
+                            *d4 = far4;
+                            const uint32_t e[4] = {d.x, d.y, d.z, d.w};
+                            uint32_t l[4] = {0u, 0u, 0u, 0u};
+                            if (KIND == kExhL1) {
+                                uint4 *const l4 =
+                                    reinterpret_cast<uint4 *>(sl + pp * kExhRange) + v4;
+                                const uint4 lv = *l4;
+                                *l4 = far4;
+                                l[0] = lv.x;
+                                l[1] = lv.y;
+                                l[2] = lv.z;
+                                l[3] = lv.w;
+                            }
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                const float f = __uint_as_float(e[c]);
+                                err[4 * q + c] +=
+                                    KIND == kExhDist
+                                        ? rho(g.metric, f, f, f, g.eps, g.tau, g.lp)
+                                        : (KIND == kExhSquare ? fminf(f, g.tau * g.tau)
+                                                              : fminf(__uint_as_float(l[c]), g.tau));
+                                inl[4 * q + c] += (e[c] - limbits) >> 31;      // e < limbits
+                            }
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int q = 0; q < 4 * kExhOwn; ++q) {
+                const uint32_t at = 4u * (uint32_t)(tid + q / 4 * kBlock) + (uint32_t)(q & 3);
+                if (at < count && exh_better(be, bi, bu, err[q], (int)inl[q], u0 + at)) {
+                    be = err[q];
+                    bi = (int)inl[q];
+                    bu = u0 + at;
+                }
+            }
+        }
+        exh_record(a, k, be, bi, bu, re, ri, ru);
+    }
+}
+
+// Which form: the scatter's work per (rotation, source point) is the candidate
+// translations m side^3 and the sum over T, the query's T times nine rows.  Measured
+// (query / scatter, ms): m side^3 = 0.7 T 2.73 / 0.39 (64 x 256 points), 9 T 0.38 /
+// 0.06 (30 x 1,000), 21 T 0.35 / 0.30 (tau = 2.2 delta), 39 T 2.72 / 8.9 (side 11); at
+// side 3, where most of a point's candidates fall away with their row, 22 T 2.68 /
+// 0.75, 57 T 0.13 / 0.08, 325 T 1.18 / 0.92.
+static bool exhaustive_by_scatter(const SweepArgs &a)
+{
+    const double side = 2.0 * (double)a.g.r / a.g.delta + 1.0;
+    const double T = (double)a.g.size[0] * a.g.size[1] * a.g.size[2];
+    return a.g.m <= 1 << 20 && a.g.m * side * side * side <= (side <= 3.5 ? 300.0 : 25.0) * T;
 }
 
 hipError_t launch_exhaustive(const SweepArgs &a, int scorer, int grid, hipStream_t stream)
@@ -1908,6 +2131,16 @@ hipError_t launch_exhaustive(const SweepArgs &a, int scorer, int grid, hipStream
     if (a.k <= 0) return hipSuccess;
     if (a.g.n > kExhaustiveMaxSrc) return hipErrorInvalidValue;
     if (grid > a.k) grid = a.k;
+    if (scorer != DSES_SCORER_BRUTE && exhaustive_by_scatter(a)) {
+        const dim3 b(grid), t(kBlock);
+        if (a.g.metric == DSES_TRUNC_L1)
+            hipLaunchKernelGGL(k_exhaustive_scatter<kExhL1>, b, t, 0, stream, a);
+        else if (a.g.metric == DSES_TLS)
+            hipLaunchKernelGGL(k_exhaustive_scatter<kExhSquare>, b, t, 0, stream, a);
+        else
+            hipLaunchKernelGGL(k_exhaustive_scatter<kExhDist>, b, t, 0, stream, a);
+        return hipGetLastError();
+    }
     if (scorer == DSES_SCORER_BRUTE)
         hipLaunchKernelGGL(k_exhaustive<DSES_SCORER_BRUTE>, dim3(grid), dim3(kBlock), 0, stream, a);
     else

@@ -68,3 +68,28 @@ def test_exhaustive_rejects_unsupported_options():
     big = np.zeros((12289, 3), np.float32)
     with pytest.raises(dses.DsesError):
         dses.register_exhaustive(big, p.tgt, p.rotations, p.eps)
+
+
+# n: not a multiple of the points taken at a time; boxes of one range of translations
+# and of several; lattice pitch above, at and below the search radius; every metric
+@pytest.mark.parametrize("metric,n,m,eps,box,kw", [
+    ("trunc_l2", 5, 70, 0.05, 0.5, {}), ("trunc_l2", 18, 300, 0.05, 0.7, {}),
+    ("tls", 7, 129, 0.05, 0.6, {}), ("tls", 9, 64, 0.05, 0.4, {"tau": 0.08}),
+    ("trunc_l1", 6, 200, 0.05, 0.6, {}), ("trunc_l1", 3, 65, 0.04, 0.5, {"tau": 0.02}),
+    ("inliers", 10, 90, 0.06, 0.5, {"delta_t": 0.03}),
+    ("trunc_lp", 4, 80, 0.03, 0.6, {"delta_t": 0.06, "lp": 0.5}),
+    ("trunc_l2", 1, 1, 0.3, 0.9, {}), ("trunc_l2", 4, 40, 0.05, 0.02, {}),
+])
+def test_scattered_distances_equal_brute_force(metric, n, m, eps, box, kw):
+    """The cell-grid scorer's search may go from reference points to translations instead
+    of from queries to reference points: its records equal the brute-force scorer's
+    bit for bit (a distance beyond max(eps, tau) changes no term)."""
+    rng = np.random.default_rng(31 * n + m)
+    shape = synth.multi_primitive_shape(rng)
+    tgt = synth.sample_surface(rng, shape, m).astype(np.float32)
+    src = synth.sample_surface(rng, shape, n).astype(np.float32)
+    rot = synth.random_rotations(rng, 3).reshape(-1, 9).astype(np.float32)
+    a, b = (dses.register_exhaustive(src, tgt, rot, eps, metric, t_min=-box, t_max=box,
+                                     scorer=s, records=True, **kw) for s in ("grid", "brute"))
+    assert a.records.tobytes() == b.records.tobytes()
+    assert (a.rot_index, a.error, a.inliers) == (b.rot_index, b.error, b.inliers)
