@@ -630,9 +630,15 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     const float *ht = job.target ? job.target->host_aos.data() : job.host_tgt;
     if (!ht) {
         host_copy.resize(3 * m);
-        DSES_HIP(hipMemcpyAsync(host_copy.data(), job.tgt, 3 * m * sizeof(float),
-                                hipMemcpyDeviceToHost, stream));
+        const size_t tb = 3 * m * sizeof(float);
+        void *to = host_copy.data();
+        if (!arena) {                          // through pinned memory: one copy, one wait
+            if ((st = c->host_stage.ensure(tb)) != DSES_OK) return st;
+            to = c->host_stage.ptr;
+        }
+        DSES_HIP(hipMemcpyAsync(to, job.tgt, tb, hipMemcpyDeviceToHost, stream));
         DSES_HIP(hipStreamSynchronize(stream));
+        if (!arena) std::memcpy(host_copy.data(), to, tb);
         for (float v : host_copy)
             if (!(std::fabs(v) <= ref_coord_limit(p))) {
                 set_error("reference coordinate is non-finite or too large for the lattice");
@@ -665,10 +671,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     const bool sorted = job.n <= kSortMax && ref_x_range(ht, *perm, p.delta, p.klo[0], &ylo, &yhi);
     const int grid = std::max(1, std::min(job.k, c->n_cu));
     void *d_perm = nullptr, *d_scratch = nullptr, *d_yq = nullptr, *d_yt = nullptr;
-    void *d_rec = nullptr, *d_res = nullptr, *d_status = nullptr;
-    if ((st = dbuf(c->perm, m * sizeof(int32_t), &d_perm)) != DSES_OK) return st;
-    DSES_HIP(hipMemcpyAsync(d_perm, perm->data(), m * sizeof(int32_t), hipMemcpyHostToDevice,
-                            stream));
+    void *d_rec = nullptr, *d_status = nullptr;
     if (sorted && (st = dbuf(c->scratch, (size_t)grid * slot_words(job.n) * sizeof(int32_t),
                              &d_scratch)) != DSES_OK)
         return st;
@@ -680,9 +683,6 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         d_rec = records;
     else if ((st = dbuf(c->rec, (size_t)job.k * sizeof(dses_record), &d_rec)) != DSES_OK)
         return st;
-    if ((st = dbuf(c->res, sizeof(DevResult), &d_res)) != DSES_OK) return st;
-    if ((st = dbuf(c->status, 64, &d_status)) != DSES_OK) return st;
-    uint32_t *bad = static_cast<uint32_t *>(d_status);
 
     SweepArgs a{};
     a.src = job.src;
@@ -697,39 +697,14 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
     a.gref = choose_gref(g, sorted, ref_x_extent(ylo, yhi), o.lane_group);
 
+    HostGrid hg;                               // of a reference that is not resident
     if (scorer == DSES_SCORER_GRID) {
         const TargetRes *t = job.target;
         if (t) {
             if ((st = ensure_target_grid(const_cast<TargetRes *>(t), p.r, &a.grid)) != DSES_OK)
                 return st;
         } else {
-            HostGrid hg;
             if ((st = build_grid(ht, job.m, p.r, &hg)) != DSES_OK) return st;
-            const size_t pb = hg.pts.size() * sizeof(float), sb = hg.start.size() * sizeof(int32_t);
-            void *d_pts = nullptr, *d_start = nullptr;
-            if ((st = dbuf(c->grid_pts, pb, &d_pts)) != DSES_OK) return st;
-            if ((st = dbuf(c->grid_start, sb, &d_start)) != DSES_OK) return st;
-            if (arena) {
-                // no pinned staging: the copies read the host vectors, which live
-                // until this call's final synchronisation
-                DSES_HIP(hipMemcpyAsync(d_pts, hg.pts.data(), pb, hipMemcpyHostToDevice, stream));
-                DSES_HIP(hipMemcpyAsync(d_start, hg.start.data(), sb, hipMemcpyHostToDevice,
-                                        stream));
-                DSES_HIP(hipStreamSynchronize(stream));
-            } else {
-                // through pinned staging: the copies stay asynchronous (the buffer is
-                // reused by the next call only after this call's final synchronisation)
-                if ((st = c->host_stage.ensure(pb + sb)) != DSES_OK) return st;
-                char *hs = static_cast<char *>(c->host_stage.ptr);
-                std::memcpy(hs, hg.pts.data(), pb);
-                std::memcpy(hs + pb, hg.start.data(), sb);
-                DSES_HIP(hipMemcpyAsync(d_pts, hs, pb, hipMemcpyHostToDevice, stream));
-                DSES_HIP(hipMemcpyAsync(d_start, hs + pb, sb, hipMemcpyHostToDevice, stream));
-            }
-            a.grid.pts = static_cast<float *>(d_pts);
-            a.grid.start = static_cast<int32_t *>(d_start);
-            for (int q = 0; q < 3; ++q) { a.grid.lo[q] = hg.lo[q]; a.grid.dim[q] = hg.dim[q]; }
-            a.grid.inv = hg.inv;
         }
     } else if (scorer == DSES_SCORER_DF) {
         const TargetRes *t = job.target;
@@ -738,6 +713,56 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         a.field.r = t->df_r;
         a.field.lookup = job.p.df_lookup;
         for (int q = 0; q < 3; ++q) { a.field.lo[q] = t->df_lo[q]; a.field.inv[q] = t->df_inv[q]; }
+    }
+
+    // What the host prepared, on the device: the status words (zero), the order by x and
+    // the cell grid.  Small calls are bound by launches, copies and waits, so without an
+    // arena these are one block and one asynchronous copy from pinned memory, which the
+    // next call reuses only after this one's final synchronisation; the check shares a
+    // launch with the staging, the result comes back by the selection's own stores, and
+    // records on the device need no second wait: 32 x 32 points, 1,000 rotations 184 ->
+    // 131 us; Alg. 1, 32 x 32 points, 100 rotations 534 -> 478 us; 8,192 host points 3.46
+    // -> 3.32 ms.
+    const size_t pb = hg.pts.size() * sizeof(float), sb = hg.start.size() * sizeof(int32_t);
+    void *d_pts = nullptr, *d_start = nullptr;
+    if (arena) {
+        // no pinned staging: the copies read the host vectors, which live until the
+        // synchronisation
+        if ((st = dbuf(c->upload, 64, &d_status)) != DSES_OK) return st;
+        if ((st = dbuf(c->upload, m * sizeof(int32_t), &d_perm)) != DSES_OK) return st;
+        if (pb && (st = dbuf(c->upload, pb, &d_pts)) != DSES_OK) return st;
+        if (sb && (st = dbuf(c->upload, sb, &d_start)) != DSES_OK) return st;
+        DSES_HIP(launch_clear(static_cast<uint32_t *>(d_status), 16, stream));
+        DSES_HIP(hipMemcpyAsync(d_perm, perm->data(), m * sizeof(int32_t), hipMemcpyHostToDevice,
+                                stream));
+        if (pb)
+            DSES_HIP(hipMemcpyAsync(d_pts, hg.pts.data(), pb, hipMemcpyHostToDevice, stream));
+        if (sb)
+            DSES_HIP(hipMemcpyAsync(d_start, hg.start.data(), sb, hipMemcpyHostToDevice, stream));
+        if (pb) DSES_HIP(hipStreamSynchronize(stream));
+    } else {
+        auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+        const size_t o_perm = 256, o_pts = o_perm + up(m * sizeof(int32_t)),
+                     o_start = o_pts + up(pb), total = o_start + sb;
+        if ((st = c->upload.ensure(total)) != DSES_OK) return st;
+        if ((st = c->host_stage.ensure(total)) != DSES_OK) return st;
+        char *hs = static_cast<char *>(c->host_stage.ptr), *ds = static_cast<char *>(c->upload.ptr);
+        std::memset(hs, 0, o_perm);
+        std::memcpy(hs + o_perm, perm->data(), m * sizeof(int32_t));
+        if (pb) std::memcpy(hs + o_pts, hg.pts.data(), pb);
+        if (sb) std::memcpy(hs + o_start, hg.start.data(), sb);
+        DSES_HIP(hipMemcpyAsync(ds, hs, total, hipMemcpyHostToDevice, stream));
+        d_status = ds;
+        d_perm = ds + o_perm;
+        d_pts = ds + o_pts;
+        d_start = ds + o_start;
+    }
+    uint32_t *bad = static_cast<uint32_t *>(d_status);
+    if (scorer == DSES_SCORER_GRID && !job.target) {
+        a.grid.pts = static_cast<float *>(d_pts);
+        a.grid.start = static_cast<int32_t *>(d_start);
+        for (int q = 0; q < 3; ++q) { a.grid.lo[q] = hg.lo[q]; a.grid.dim[q] = hg.dim[q]; }
+        a.grid.inv = hg.inv;
     }
 
     const bool timing = c->timing_enabled;
@@ -749,16 +774,13 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     prepare.end();
     TraceRange device("dses.sweep_select");    // launches to the result on the host
     rec_ev(0);
-    DSES_HIP(launch_clear(bad, 16, stream));
-    if (check_inputs) {
-        CheckArgs ca{job.src,  job.n, job.tgt, job.m, job.rot, job.k, kSrcCoordLimit,
-                     ref_coord_limit(p), bad};
-        DSES_HIP(launch_check(ca, stream));
-    }
     const bool arrange = worth_arranging(g, a.gref, ref_x_extent(ylo, yhi), job.k);
-    DSES_HIP(launch_stage(stage_desc(g, a.gref, arrange, job.tgt, static_cast<int32_t *>(d_perm),
-                                     static_cast<int32_t *>(d_yq), static_cast<float *>(d_yt)),
-                          stream));
+    const CheckArgs ca{job.src,  job.n, job.tgt, job.m, job.rot, job.k, kSrcCoordLimit,
+                       ref_coord_limit(p), bad};
+    DSES_HIP(launch_prepare(check_inputs ? &ca : nullptr,
+                            stage_desc(g, a.gref, arrange, job.tgt, static_cast<int32_t *>(d_perm),
+                                       static_cast<int32_t *>(d_yq), static_cast<float *>(d_yt)),
+                            stream));
     rec_ev(1);
     if (job.exhaustive) {
         DSES_HIP(launch_exhaustive(a, scorer, grid, stream));
@@ -771,10 +793,21 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         DSES_HIP(launch_sweep(a, scorer, grid, stream));
     }
     rec_ev(2);
-    DSES_HIP(launch_select(a.rec, job.k, job.rot, p.delta, static_cast<DevResult *>(d_res), bad,
-                           stream));
+    // the result goes to pinned host memory by the kernel's own stores
+    DSES_HIP(launch_select(a.rec, job.k, job.rot, p.delta, c->host_res, bad, stream));
     rec_ev(3);
-    DSES_HIP(hipMemcpyAsync(c->host_res, d_res, sizeof(DevResult), hipMemcpyDeviceToHost, stream));
+    // Records for a buffer of this device are copied by a kernel that looks at the
+    // selection's outcome, so that they need no second wait; other buffers by the runtime,
+    // once the outcome is known.
+    bool publish = false;
+    if (records && on_device && records != (void *)a.rec &&
+        reinterpret_cast<uintptr_t>(records) % alignof(dses_record) == 0) {
+        hipPointerAttribute_t at{};
+        publish = hipPointerGetAttributes(&at, records) == hipSuccess &&
+                  at.type == hipMemoryTypeDevice && at.device == c->device;
+        if (!publish) (void)hipGetLastError();
+    }
+    if (publish) DSES_HIP(launch_publish(a.rec, records, job.k, bad, stream));
     DSES_HIP(hipStreamSynchronize(stream));
     device.end();
     const DevResult r = *c->host_res;
@@ -795,7 +828,8 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         set_error("no rotation received a vote inside the translation box");
         return DSES_E_NOCANDIDATE;
     }
-    if (records && records != (void *)a.rec) {
+    const bool copy_records = records && records != (void *)a.rec && !publish;
+    if (copy_records) {
         DSES_HIP(hipMemcpyAsync(records, a.rec, (size_t)job.k * sizeof(dses_record),
                                 on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                                 stream));
@@ -813,7 +847,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
             DSES_HIP(hipMemcpyAsync(o.topk, dst, (size_t)o.top_k * sizeof(dses_candidate),
                                     hipMemcpyDeviceToHost, stream));
     }
-    if (records || o.top_k > 0) DSES_HIP(hipStreamSynchronize(stream));
+    if (copy_records || o.top_k > 0) DSES_HIP(hipStreamSynchronize(stream));
     if (out) {
         std::memcpy(out->R, r.R, sizeof(out->R));
         std::memcpy(out->t, r.t, sizeof(out->t));

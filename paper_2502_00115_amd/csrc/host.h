@@ -95,11 +95,12 @@ struct Context {
     hipStream_t stream = nullptr;
     std::mutex mu;                       // serialises the plain entry points
     // workspace of the plain path
-    DevBuf in_src, in_tgt, in_rot, yq, yt, rec, res, status, grid_pts, grid_start, perm, scratch;
+    DevBuf in_src, in_tgt, in_rot, yq, yt, rec, scratch;
+    DevBuf upload;                       // status words, order by x, cell grid
     DevBuf topk_a, topk_b, topk_out;     // top-k passes and output staging
     DevBuf prune;                        // q-pruning: M* and the work cursor
     DevResult *host_res = nullptr;       // pinned
-    PinnedBuf host_stage;                // staging of host-built uploads (cell grid)
+    PinnedBuf host_stage;                // the reference as read back, then the upload
     // timing
     bool timing_enabled = false;
     std::mutex stats_mu;

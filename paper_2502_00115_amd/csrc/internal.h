@@ -205,10 +205,14 @@ struct CheckArgs {
 
 // Launchers (defined in kernels.hip); all enqueue on `stream`.
 hipError_t launch_check(const CheckArgs &a, hipStream_t stream);
-hipError_t launch_stage(const StageDesc &d, hipStream_t stream);
+// Input check (null: none; its status word must be 0) and staging, one launch and the
+// bank order's if asked for.
+hipError_t launch_prepare(const CheckArgs *check, const StageDesc &d, hipStream_t stream);
 hipError_t launch_sweep(const SweepArgs &a, int scorer, int grid, hipStream_t stream);
 hipError_t launch_select(const dses_record *rec, int32_t k, const float *rot, float delta,
-                         DevResult *res, const uint32_t *status, hipStream_t stream);
+                         DevResult *res, uint32_t *status, hipStream_t stream);
+hipError_t launch_publish(const dses_record *rec, void *out, int32_t k, const uint32_t *status,
+                          hipStream_t stream);
 // Top-k candidates of K records in selection order (k <= DSES_TOPK_MAX): passes of
 // workgroup sorts reduce 2048 entries to k each until one workgroup remains; the
 // scratch buffers hold ceil(K / 2048) * k entries of 12 bytes each.

@@ -28,6 +28,7 @@
 //    on the GPU.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <utility>
 #include <math.h>
 #include <stdint.h>
@@ -87,11 +88,12 @@ __device__ __forceinline__ int wave_isum(int v)
 // --------------------------------------------------------------------------
 // input checks (device-pointer inputs): finiteness, coordinate range, rotations
 // --------------------------------------------------------------------------
-__global__ void k_check(CheckArgs a)
+// Blocks block, block + blocks, ... of the check.
+__device__ __forceinline__ void check_inputs(const CheckArgs &a, int block, int blocks)
 {
     const int64_t total = (int64_t)a.n * 3 + (int64_t)a.m * 3 + a.k;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t e = block * (int64_t)blockDim.x + threadIdx.x; e < total;
+         e += (int64_t)blocks * blockDim.x) {
         bool bad = false;
         if (e < (int64_t)a.n * 3) {
             float v = a.src[e];
@@ -114,13 +116,17 @@ __global__ void k_check(CheckArgs a)
     }
 }
 
-hipError_t launch_check(const CheckArgs &a, hipStream_t stream)
+__global__ void k_check(CheckArgs a) { check_inputs(a, blockIdx.x, gridDim.x); }
+
+static int check_blocks(const CheckArgs &a)
 {
     const int64_t total = (int64_t)a.n * 3 + (int64_t)a.m * 3 + a.k;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 2048) blocks = 2048;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_check, dim3(blocks), dim3(256), 0, stream, a);
+    return (int)std::min<int64_t>(2048, std::max<int64_t>(1, (total + 255) / 256));
+}
+
+hipError_t launch_check(const CheckArgs &a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_check, dim3(check_blocks(a)), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -211,12 +217,6 @@ __device__ __forceinline__ void stage_point(const StageDesc &d, int j)
     int32_t *gx = d.yq + 3 * (size_t)d.m + 2 * (size_t)(j / d.gref);
     if (j % d.gref == 0) gx[0] = q[0];                  // the points are sorted by x
     if (j % d.gref == d.gref - 1 || j == d.m - 1) gx[1] = q[0];
-}
-
-__global__ void k_stage(StageDesc d)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < d.m) stage_point(d, j);
 }
 
 // --------------------------------------------------------------------------
@@ -364,9 +364,22 @@ __global__ void __launch_bounds__(kArrangeBlock) k_arrange(StageDesc d)
     arrange_group(d, blockIdx.x, P, mask);
 }
 
-hipError_t launch_stage(const StageDesc &d, hipStream_t stream)
+// Input check (blocks below `checks`) and staging in one launch.
+__global__ void k_prepare(CheckArgs c, int checks, StageDesc d)
 {
-    hipLaunchKernelGGL(k_stage, dim3((d.m + 255) / 256), dim3(256), 0, stream, d);
+    if ((int)blockIdx.x < checks) {
+        check_inputs(c, blockIdx.x, checks);
+        return;
+    }
+    const int j = ((int)blockIdx.x - checks) * blockDim.x + threadIdx.x;
+    if (j < d.m) stage_point(d, j);
+}
+
+hipError_t launch_prepare(const CheckArgs *check, const StageDesc &d, hipStream_t stream)
+{
+    const int checks = check ? check_blocks(*check) : 0;
+    hipLaunchKernelGGL(k_prepare, dim3(checks + (d.m + 255) / 256), dim3(256), 0, stream,
+                       check ? *check : CheckArgs{}, checks, d);
     const int groups = d.m / d.gref;           // a last group that is not full keeps its order
     if (d.arrange && groups > 0)
         hipLaunchKernelGGL(k_arrange, dim3(groups), dim3(kArrangeBlock), 0, stream, d);
@@ -2187,7 +2200,8 @@ __device__ __forceinline__ bool sel_better(float e, int i, int k, float oe, int 
     return ok < k;
 }
 
-__device__ void select_body(const dses_record *rec, int32_t K, const float *rot, float delta,
+// Returns in thread 0 whether there is a valid candidate.
+__device__ bool select_body(const dses_record *rec, int32_t K, const float *rot, float delta,
                             DevResult *res, const uint32_t *status, float *se, int *si, int *sk,
                             int *sv)
 {
@@ -2208,6 +2222,7 @@ __device__ void select_body(const dses_record *rec, int32_t K, const float *rot,
     }
     if (lane == 0) { se[wave] = be; si[wave] = bi; sk[wave] = bk; sv[wave] = nvalid; }
     __syncthreads();
+    bool found = false;
     if (tid == 0) {
         float e = INFINITY;
         int i = 0, k = -1, nv = 0;
@@ -2215,6 +2230,7 @@ __device__ void select_body(const dses_record *rec, int32_t K, const float *rot,
             nv += sv[w];
             if (sel_better(e, i, k, se[w], si[w], sk[w])) { e = se[w]; i = si[w]; k = sk[w]; }
         }
+        found = k >= 0;
         res->rot_index = k;
         res->n_valid = nv;
         res->bad_input = status ? status[0] : 0u;
@@ -2227,19 +2243,43 @@ __device__ void select_body(const dses_record *rec, int32_t K, const float *rot,
             for (int e2 = 0; e2 < 9; ++e2) res->R[e2] = rot[9 * (size_t)k + e2];
         }
     }
+    return found;
 }
 
+// res may be host memory mapped for the device: it is written once, by one thread.
+// status[1] tells k_publish whether the call succeeds.
 __global__ void __launch_bounds__(1024) k_select(const dses_record *rec, int32_t K,
                                                  const float *rot, float delta, DevResult *res,
-                                                 const uint32_t *status)
+                                                 uint32_t *status)
 {
     __shared__ float se[16];
     __shared__ int si[16], sk[16], sv[16];
-    select_body(rec, K, rot, delta, res, status, se, si, sk, sv);
+    const bool found = select_body(rec, K, rot, delta, res, status, se, si, sk, sv);
+    if (threadIdx.x == 0) status[1] = found && status[0] == 0u ? 1u : 0u;
+}
+
+// The records to the caller's device buffer, if the selection found a candidate in
+// valid inputs (no synchronisation before the copy).
+__global__ void k_publish(const uint32_t *rec, uint32_t *out, int64_t words, const uint32_t *status)
+{
+    if (status[1] == 0u) return;
+    for (int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; w < words;
+         w += (int64_t)gridDim.x * blockDim.x)
+        out[w] = rec[w];
+}
+
+hipError_t launch_publish(const dses_record *rec, void *out, int32_t k, const uint32_t *status,
+                          hipStream_t stream)
+{
+    const int64_t words = (int64_t)k * (int64_t)(sizeof(dses_record) / 4);
+    hipLaunchKernelGGL(k_publish, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 1024)),
+                       dim3(256), 0, stream, reinterpret_cast<const uint32_t *>(rec),
+                       static_cast<uint32_t *>(out), words, status);
+    return hipGetLastError();
 }
 
 hipError_t launch_select(const dses_record *rec, int32_t k, const float *rot, float delta,
-                         DevResult *res, const uint32_t *status, hipStream_t stream)
+                         DevResult *res, uint32_t *status, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, stream, rec, k, rot, delta, res,
                        status);

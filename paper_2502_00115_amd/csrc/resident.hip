@@ -112,8 +112,9 @@ dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, i
     hipError_t e = dev_alloc(&st.yq, 4 * stage_words(m));
     if (e == hipSuccess) e = dev_alloc(&st.yt, 12 * m);
     if (e == hipSuccess)
-        e = launch_stage(stage_desc(g, gref, gref != 0, tm->aos, tm->d_perm, st.yq, st.yt),
-                         stream);
+        e = launch_prepare(nullptr,
+                           stage_desc(g, gref, gref != 0, tm->aos, tm->d_perm, st.yq, st.yt),
+                           stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {
         if (st.yq) (void)hipFree(st.yq);
