@@ -196,18 +196,17 @@ dses_status dses_target_create(const float *tgt, int64_t m, const dses_target_op
         }
         HostGrid hg;
         if ((st = build_grid(T.host_aos.data(), T.m, r, &hg)) != DSES_OK) return fail(st);
-        float *gp = nullptr;
-        int32_t *gs = nullptr;
+        float *gp = nullptr;                   // the grid's points, then its cell starts
         const size_t nvox = (size_t)res * res * res;
-        if (dev_alloc(&gp, hg.pts.size() * sizeof(float)) != hipSuccess ||
-            dev_alloc(&gs, hg.start.size() * sizeof(int32_t)) != hipSuccess ||
+        if (dev_alloc(&gp, hg.pts.size() * sizeof(float) + hg.start.size() * sizeof(int32_t)) !=
+                hipSuccess ||
             dev_alloc(&T.df, nvox * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             if (gp) (void)hipFree(gp);
-            if (gs) (void)hipFree(gs);
             set_error("device allocation for the distance field failed");
             return fail(DSES_E_NOMEM);
         }
+        auto *gs = reinterpret_cast<int32_t *>(gp + hg.pts.size());
         hipError_t e = hipMemcpy(gp, hg.pts.data(), hg.pts.size() * sizeof(float),
                                  hipMemcpyHostToDevice);
         if (e == hipSuccess)
@@ -217,7 +216,6 @@ dses_status dses_target_create(const float *tgt, int64_t m, const dses_target_op
             e = launch_df_build(gp, gs, hg, res, T.df_lo, T.df_h, r, T.df, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         (void)hipFree(gp);
-        (void)hipFree(gs);
         if (e != hipSuccess) {
             set_error(std::string("distance field build failed: ") + hipGetErrorString(e));
             return fail(DSES_E_DEVICE);

@@ -95,3 +95,15 @@ def test_bank_order_does_not_change_records(n, m, eps, k, lg):
     for lo in range(0, k, k // 4):
         part = dses.register(src, tgt, rot[lo:lo + 16], eps, records=True, lane_group=lg)
         assert part.records.tobytes() == got.records[lo:lo + 16].tobytes()
+
+
+@pytest.mark.parametrize("m", [511, 512, 513, 3000])
+def test_equal_and_signed_x(m):
+    """Reference points that share their x (both zeros among them), on both sides of the
+    size from which the order by x is made by counting."""
+    src, tgt, rot = _clouds(120, m, 21)
+    tgt[:, 0] = np.float32(0.037) * np.round(tgt[:, 0] / np.float32(0.037))
+    tgt[::2, 0] *= np.where(tgt[::2, 0] == 0, np.float32(-1), np.float32(1))
+    ref = oracle.records(src, tgt, rot, 0.04)
+    got = dses.register(src, tgt, rot, 0.04, records=True)
+    compare_records(got.records, ref, 120, label=f"m={m}")
