@@ -267,6 +267,69 @@ int choose_gref(const Geom &g, bool sorted, float x_extent, int asked)
     return 64.0f * x_extent <= 0.13f * (float)g.pps * (float)g.m ? 64 : 32;
 }
 
+// A workgroup holds a compute unit, so k rotations run in ceil(k / CUs) rounds and the
+// last may be nearly empty.  Items of fewer slabs fill it; each repeats the sort of the
+// sources, and the scores move to a launch of their own.  The estimate is the largest
+// sum of a workgroup's items, in cycles: a compute unit votes about 8.5 pairs per cycle,
+// a slab's clear, waits and scan take about 8,000, a sort 8,000 and 3 per source, the
+// second launch 24,000.  The votes are spread over the slabs as the differences of two
+// clouds of the reference's x extent (a triangle; the middle slabs hold most), about the
+// box's middle or a quarter of the box to either side: where the clouds lie is not known
+// here, and two slabs of which one holds most votes lose by being two items.
+// Measured (ms, whole / in parts): 2,000 x 8,192 points at 0.03, 100 rotations 1.32 /
+// 0.82, 300 rotations 2.33 / 1.63, 576 rotations 3.15 / 2.50; 4,096 x 16,384 points 4.21 / 2.23,
+// 7.55 / 4.88, 10.77 / 8.23; 1,000 x 8,192 points at 0.05 (two slabs), 576 rotations 1.83 /
+// 1.98, so the rule leaves it whole.
+int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu)
+{
+    constexpr int kMostParts = 16, kProbes = 16;
+    const int slabs = (g.size[0] + g.pps - 1) / g.pps;
+    if (slabs < 2 || k > 8 * n_cu) return 1;       // at most one round of nine to gain
+    const double width = std::max(1.0, (double)x_extent);
+    auto below = [&](double x) {                   // share of the differences below x bins
+        const double u = std::min(1.0, std::max(-1.0, x / width));
+        return u < 0 ? 0.5 * (1 + u) * (1 + u) : 1 - 0.5 * (1 - u) * (1 - u);
+    };
+    const double pairs = (double)g.n * g.m / 8.5, sort = 8000.0 + 3.0 * g.n;
+    auto slab = [&](int s, double shift) {
+        const double x0 = s * g.pps - 0.5 * g.size[0] + shift;
+        return 8000.0 + pairs * (below(x0 + g.pps) - below(x0));
+    };
+    auto cost = [&](int parts, double shift) {
+        double item[kMostParts], most = 0;
+        for (int p = 0; p < parts; ++p) {
+            item[p] = sort;
+            for (int s = p; s < slabs; s += parts) item[p] += slab(s, shift);
+        }
+        const int64_t all = (int64_t)k * parts;
+        for (int q = 0; q < kProbes; ++q) {        // workgroups q n_cu / 16
+            const int64_t b = (int64_t)q * n_cu / kProbes;
+            if (b >= all) break;
+            double sum = 0;
+            for (int p = 0; p < parts; ++p) {      // its items b, b + n_cu, ... of part p
+                auto upto = [&](int64_t e) { return e > b ? (e - b + n_cu - 1) / n_cu : 0; };
+                sum += item[p] * (double)(upto((int64_t)(p + 1) * k) - upto((int64_t)p * k));
+            }
+            most = std::max(most, sum);
+        }
+        return most + (parts > 1 ? 24000.0 : 0.0);
+    };
+    double least = 0.92;
+    int best = 1;
+    for (int parts = 2; parts <= std::min(slabs, kMostParts); ++parts) {
+        double share = 0;                          // of the time in one piece
+        for (int side = -1; side <= 1; ++side) {
+            const double shift = 0.25 * side * g.size[0];
+            share = std::max(share, cost(parts, shift) / cost(1, shift));
+        }
+        if (share < least) {
+            least = share;
+            best = parts;
+        }
+    }
+    return best;
+}
+
 StageDesc stage_desc(const Geom &g, int gref, bool arrange, const float *tgt, const int32_t *perm,
                      int32_t *yq, float *yt)
 {
@@ -704,13 +767,20 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     }
     int32_t ylo = 0, yhi = 0;
     const bool sorted = job.n <= kSortMax && ref_x_range(ht, *perm, p.delta, p.klo[0], &ylo, &yhi);
-    const int grid = std::max(1, std::min(job.k, c->n_cu));
+    const int gref = choose_gref(g, sorted, ref_x_extent(ylo, yhi), o.lane_group);
+    const int parts = gref && !arena && !job.exhaustive && !(o.q > 0.0f)
+                          ? choose_parts(g, job.k, ref_x_extent(ylo, yhi), c->n_cu)
+                          : 1;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)job.k * parts, c->n_cu));
     void *d_perm = nullptr, *d_scratch = nullptr, *d_yq = nullptr, *d_yt = nullptr;
     void *d_rec = nullptr, *d_status = nullptr;
     if (sorted && (st = dbuf(c->scratch, (size_t)grid * slot_words(job.n) * sizeof(int32_t),
                              &d_scratch)) != DSES_OK)
         return st;
 
+    if (parts > 1 &&
+        (st = c->modes.ensure((size_t)job.k * parts * 2 * sizeof(uint32_t))) != DSES_OK)
+        return st;
     if ((st = dbuf(c->yq, stage_words(m) * sizeof(int32_t), &d_yq)) != DSES_OK) return st;
     if ((st = dbuf(c->yt, 3 * m * sizeof(float), &d_yt)) != DSES_OK) return st;
     // with an arena the records go straight to the caller's buffer when it gives one
@@ -730,7 +800,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     a.scratch = sorted ? static_cast<int32_t *>(d_scratch) : nullptr;
     a.scratch_stride = job.n;
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-    a.gref = choose_gref(g, sorted, ref_x_extent(ylo, yhi), o.lane_group);
+    a.gref = gref;
 
     HostGrid hg;                               // of a reference that is not resident
     if (scorer == DSES_SCORER_GRID) {
@@ -824,6 +894,8 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         uint32_t *pw = static_cast<uint32_t *>(c->prune.ptr);
         DSES_HIP(launch_sweep(a, kScoreNone, grid, stream));
         DSES_HIP(launch_score_pruned(a, scorer, o.q, pw, pw + 1, grid, stream));
+    } else if (parts > 1) {
+        DSES_HIP(launch_sweep_parts(a, scorer, grid, c->modes.ptr, parts, stream));
     } else {
         DSES_HIP(launch_sweep(a, scorer, grid, stream));
     }

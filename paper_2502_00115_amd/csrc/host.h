@@ -96,6 +96,7 @@ struct Context {
     std::mutex mu;                       // serialises the plain entry points
     // workspace of the plain path
     DevBuf in_src, in_tgt, in_rot, yq, yt, rec, scratch;
+    DevBuf modes;                        // sweeps of few rotations: the mode of each part
     DevBuf upload;                       // status words, order by x, cell grid
     DevBuf topk_a, topk_b, topk_out;     // top-k passes and output staging
     DevBuf prune;                        // q-pruning: M* and the work cursor
@@ -157,6 +158,8 @@ inline int choose_batch_gref(const Geom &g, bool sorted, float x_extent)
 }
 // Staging of a reference of g.m points for a vote of geometry g with lane groups of
 // gref points (0: the general path), in bank order if `arrange`.
+// Items a rotation's slabs are split into by the plain path (1: none).
+int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu);
 StageDesc stage_desc(const Geom &g, int gref, bool arrange, const float *tgt, const int32_t *perm,
                      int32_t *yq, float *yt);
 // Whether a call of k rotations gains from bank order (k_arrange takes 20 us for

@@ -211,6 +211,9 @@ hipError_t launch_prepare(const CheckArgs *check, const StageDesc &d, hipStream_
 hipError_t launch_sweep(const SweepArgs &a, int scorer, int grid, hipStream_t stream);
 hipError_t launch_select(const dses_record *rec, int32_t k, const float *rot, float delta,
                          DevResult *res, uint32_t *status, hipStream_t stream);
+// The sweep with each rotation's slabs in `parts` items (choose_parts).
+hipError_t launch_sweep_parts(const SweepArgs &a, int scorer, int grid, void *modes, int parts,
+                              hipStream_t stream);
 hipError_t launch_publish(const dses_record *rec, void *out, int32_t k, const uint32_t *status,
                           hipStream_t stream);
 // Top-k candidates of K records in selection order (k <= DSES_TOPK_MAX): passes of

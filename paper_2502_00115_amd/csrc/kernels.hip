@@ -1647,8 +1647,11 @@ __device__ __forceinline__ void vote_slab_any(const SweepArgs *args, int32_t *sp
 
 // Vote, mode and score one rotation k with the whole workgroup; sp is the
 // workgroup's source-sort scratch (null: sources not sorted).  Writes a.rec[k].
-template <int CW, int SCORER, int GREF>
-__device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t *lds, int32_t *sp)
+// Slabs first, first + step, ... of rotation k (all of them unless PART): the largest
+// count and the lowest position that holds it, for every thread.
+template <int CW, int GREF, bool PART>
+__device__ __forceinline__ void vote_mode(const SweepArgs *args, int k, uint32_t *lds, int32_t *sp,
+                                          int first, int step, uint32_t &best_c, uint32_t &best_p)
 {
     uint32_t *hist = lds;
     uint32_t *scr = lds + kHistWordsMax;          // kScratchWords words
@@ -1667,10 +1670,11 @@ __device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t
     for (int w = tid; w < (g.slab_words + 3) >> 2; w += kBlock) h4[w] = make_uint4(0, 0, 0, 0);
     if (tid == 0) scr[kUnitCounter] = 0u;
     __syncthreads();
-    uint32_t best_c = 0, wave_p = 0xFFFFFFFFu;
+    best_c = 0;
+    uint32_t wave_p = 0xFFFFFFFFu;
     const int size_x = g.size[0], pps = g.pps;
     const uint32_t plane = Sy * RW;
-    for (int x0 = 0; x0 < size_x; x0 += pps) {
+    for (int x0 = PART ? first * pps : 0; x0 < size_x; x0 += PART ? step * pps : pps) {
         const int np = min(pps, size_x - x0);
         if (GREF)
             vote_windows<CW, GREF ? GREF : 64>(args, sp, x0, np, hist);
@@ -1694,13 +1698,19 @@ __device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t
     }
     if ((tid & 63) == 0) scr[24 + (tid >> 6)] = wave_p;
     __syncthreads();
-    uint32_t best_p = 0xFFFFFFFFu;
+    best_p = 0xFFFFFFFFu;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) best_p = min(best_p, scr[24 + w]);
     best_p = (uint32_t)uni((int)best_p);
+}
 
+// The record of rotation k from its largest count and that count's lowest position.
+template <int CW, int SCORER>
+__device__ __forceinline__ void score_mode(const SweepArgs *args, int k, uint32_t *lds,
+                                           uint32_t best_c, uint32_t best_p)
+{
     if (best_c == 0) {
-        if (tid == 0) {
+        if (threadIdx.x == 0) {
             dses_record rec;
             rec.bin[0] = rec.bin[1] = rec.bin[2] = 0;
             rec.votes = 0;
@@ -1721,6 +1731,14 @@ __device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t
     score_candidate<SCORER>(args, k, bx, by, bz, best_c, lds);
 }
 
+template <int CW, int SCORER, int GREF>
+__device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t *lds, int32_t *sp)
+{
+    uint32_t best_c, best_p;
+    vote_mode<CW, GREF, false>(args, k, lds, sp, 0, 1, best_c, best_p);
+    score_mode<CW, SCORER>(args, k, lds, best_c, best_p);
+}
+
 // A kernel's by-value argument as a pointer for phase_args.
 __device__ __forceinline__ const SweepArgs *kernel_args()
 {
@@ -1735,6 +1753,91 @@ __global__ void __launch_bounds__(kBlock) k_sweep(SweepArgs a)
                             : nullptr;
     for (int k = blockIdx.x; k < a.k; k += gridDim.x)
         sweep_one<CW, SCORER, GREF>(kernel_args(), k, lds, sp);
+}
+
+// Few rotations: slabs p, p + parts, ... of each are an item of their own (the middle
+// slabs, which hold most votes, go to different items), so that the last round of
+// workgroups is not nearly empty (or, with fewer rotations than compute units, the
+// first).  An item leaves its largest count and lowest position
+// in modes[part * K + k]; k_score_modes scores the largest of a rotation's.  Bound by the
+// vote as k_sweep is; each item repeats the sort of the sources.
+template <int CW, int GREF>
+__global__ void __launch_bounds__(kBlock) k_sweep_parts(SweepArgs a, uint2 *modes, int parts)
+{
+    __shared__ __align__(16) uint32_t lds[kLdsWords];
+    int32_t *sp = a.scratch + (size_t)blockIdx.x * slot_words(a.scratch_stride);
+    for (int part = 0, k = blockIdx.x;; k += gridDim.x) {
+        while (k >= a.k) {
+            k -= a.k;
+            ++part;
+        }
+        if (part >= parts) break;
+        uint32_t best_c, best_p;
+        vote_mode<CW, GREF, true>(kernel_args(), k, lds, sp, part, parts, best_c, best_p);
+        if (threadIdx.x == 0) modes[(size_t)part * a.k + k] = make_uint2(best_c, best_p);
+    }
+}
+
+template <int CW, int SCORER>
+__global__ void __launch_bounds__(kBlock) k_score_modes(SweepArgs a, const uint2 *modes, int parts)
+{
+    __shared__ __align__(16) uint32_t lds[kLdsWords];
+    for (int k = blockIdx.x; k < a.k; k += gridDim.x) {
+        uint32_t best_c = 0, best_p = 0xFFFFFFFFu;
+        for (int part = 0; part < parts; ++part) {
+            const uint2 o = modes[(size_t)part * a.k + k];
+            if (o.x > best_c || (o.x == best_c && o.y < best_p)) { best_c = o.x; best_p = o.y; }
+        }
+        score_mode<CW, SCORER>(kernel_args(), k, lds, (uint32_t)uni((int)best_c),
+                               (uint32_t)uni((int)best_p));
+        __syncthreads();                                 // its LDS is reused
+    }
+}
+
+template <int CW>
+static hipError_t launch_parts(const SweepArgs &a, int scorer, int grid, uint2 *modes, int parts,
+                               hipStream_t stream)
+{
+    if (a.gref == 32)
+        hipLaunchKernelGGL((k_sweep_parts<CW, 32>), dim3(grid), dim3(kBlock), 0, stream, a, modes,
+                           parts);
+    else
+        hipLaunchKernelGGL((k_sweep_parts<CW, 64>), dim3(grid), dim3(kBlock), 0, stream, a, modes,
+                           parts);
+    const dim3 blocks(std::min(grid, a.k));
+    switch (scorer) {
+    case kScoreNone:
+        hipLaunchKernelGGL((k_score_modes<CW, kScoreNone>), blocks, dim3(kBlock), 0, stream, a,
+                           modes, parts);
+        break;
+    case kScoreVotes:
+        hipLaunchKernelGGL((k_score_modes<CW, kScoreVotes>), blocks, dim3(kBlock), 0, stream, a,
+                           modes, parts);
+        break;
+    case DSES_SCORER_BRUTE:
+        hipLaunchKernelGGL((k_score_modes<CW, DSES_SCORER_BRUTE>), blocks, dim3(kBlock), 0, stream,
+                           a, modes, parts);
+        break;
+    case DSES_SCORER_GRID:
+        hipLaunchKernelGGL((k_score_modes<CW, DSES_SCORER_GRID>), blocks, dim3(kBlock), 0, stream,
+                           a, modes, parts);
+        break;
+    default:
+        hipLaunchKernelGGL((k_score_modes<CW, DSES_SCORER_DF>), blocks, dim3(kBlock), 0, stream, a,
+                           modes, parts);
+    }
+    return hipGetLastError();
+}
+
+// modes: parts * a.k entries; a.scratch holds one slot per workgroup of the grid.
+hipError_t launch_sweep_parts(const SweepArgs &a, int scorer, int grid, void *modes, int parts,
+                              hipStream_t stream)
+{
+    if (a.k <= 0) return hipSuccess;
+    if (!a.scratch || !a.gref || parts < 1 || parts > a.g.nslabs) return hipErrorInvalidValue;
+    return a.g.counter_bits == 16
+               ? launch_parts<16>(a, scorer, grid, static_cast<uint2 *>(modes), parts, stream)
+               : launch_parts<32>(a, scorer, grid, static_cast<uint2 *>(modes), parts, stream);
 }
 
 template <int CW, int SC>

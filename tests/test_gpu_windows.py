@@ -107,3 +107,23 @@ def test_equal_and_signed_x(m):
     ref = oracle.records(src, tgt, rot, 0.04)
     got = dses.register(src, tgt, rot, 0.04, records=True)
     compare_records(got.records, ref, 120, label=f"m={m}")
+
+
+@pytest.mark.parametrize("n,m,eps,scorer,metric", [
+    (300, 8192, 0.03, "grid", "trunc_l2"), (300, 8192, 0.03, "df", "trunc_l2"),
+    (1000, 2500, 0.05, "brute", "trunc_l1"), (2600, 4097, 0.03, "grid", "votes"),
+    (500, 3000, 0.13, "grid", "tls"), (400, 3000, 0.01, "grid", "inliers"),
+])
+def test_slabs_in_parts(n, m, eps, scorer, metric):
+    """Calls of few rotations, whose slabs may go to several workgroups (two slabs at the
+    coarsest lattice, a box of one plane per slab at the finest), give the records of the
+    same rotations inside a list that fills the device for whole rounds."""
+    src, tgt, _ = _clouds(n, m, 33)
+    rot = synth.random_rotations(np.random.default_rng(2), 2048).reshape(-1, 9).astype(np.float32)
+    target = dses.Target(tgt, df_trunc=eps if scorer == "df" else 0.0)
+    box = dict(t_min=-0.6, t_max=0.6) if eps < 0.02 else {}
+    run = lambda r: dses.register_resident(target, dses.RotationSet(r), src, eps, metric,
+                                           scorer=scorer, records=True, **box).records
+    want = run(rot)
+    for k in (1, 3, 100, 257, 300, 576):
+        assert run(rot[:k]).tobytes() == want[:k].tobytes(), k
