@@ -381,7 +381,7 @@ typedef struct {
  * of the same class (same count and scorer, same power-of-two bucket of total
  * pairs, of mean source size and of mean rotation count), and then runs the batch
  * with it.  Without the flag a batch uses its class's tuned layout if one exists,
- * else the default (items_per_cu 24, vote_parts automatic). */
+ * else the default (items_per_cu 96, vote_parts automatic). */
 dses_status dses_register_batch(const dses_problem *probs, int32_t count,
                                 const dses_batch_opts *opt, dses_result *out,
                                 dses_status *status);

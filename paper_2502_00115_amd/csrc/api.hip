@@ -825,9 +825,9 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     // arena these are one block and one asynchronous copy from pinned memory, which the
     // next call reuses only after this one's final synchronisation; the check shares a
     // launch with the staging, the result comes back by the selection's own stores, and
-    // records on the device need no second wait: 32 x 32 points, 1,000 rotations 184 ->
-    // 131 us; Alg. 1, 32 x 32 points, 100 rotations 534 -> 478 us; 8,192 host points 3.46
-    // -> 3.32 ms.
+    // records on the device need no second wait: 64 x 256 points, 577 rotations 184 ->
+    // 131 us; Alg. 1 over the same sizes and 21^3 translations 534 -> 478 us; 501 x 1,531
+    // host points, 9,973 rotations 3.46 -> 3.32 ms.
     const size_t pb = hg.pts.size() * sizeof(float), sb = hg.start.size() * sizeof(int32_t);
     void *d_pts = nullptr, *d_start = nullptr;
     if (arena) {
