@@ -158,10 +158,12 @@ typedef struct {
     int32_t lane_group;       /* vote layout (sources up to 16,384 points): reference
                                  points per lane group, 32 or 64 (a wave holds four
                                  copies of the group, each streaming alternate
-                                 4-source pieces of its window); 16 is taken as 32;
-                                 0 -> chosen per call from the sizes and the
-                                 reference's extent.  Results do not depend on it;
-                                 other values are DSES_E_INVAL                        */
+                                 4-source pieces of its window; 16 is taken as 32),
+                                 or, for lattices with more than 65,535 bytes of
+                                 counters in an x plane, 16, 32 or 64 (a wave holds
+                                 128 / lane_group copies); 0 -> chosen per call from
+                                 the sizes and the reference's extent.  Results do
+                                 not depend on it; other values are DSES_E_INVAL      */
     int32_t df_lookup;        /* dses_df_lookup of the DF scorer; 0 -> NEAREST         */
 } dses_options;
 
@@ -359,8 +361,10 @@ typedef struct {
     int32_t tile_rot;         /* rotations per work item; 0 -> tuned or default layout */
     int32_t vote_parts;       /* vote work units per lane group (parts of its
                                  stream window, 1..16, rounded down to a power of
-                                 two); 0 -> tuned or automatic (about 96 units per
-                                 slab, at most 8 parts, per problem)                */
+                                 two but on the wide planes and unsorted sources of
+                                 the general vote); 0 -> tuned or automatic (about
+                                 96 units per slab, 64 in the general vote, at most
+                                 8 parts, per problem)                              */
     void *stream;
     int32_t df_lookup;        /* dses_df_lookup for DF-scored problems; 0 -> NEAREST  */
 } dses_batch_opts;
@@ -372,7 +376,7 @@ typedef struct {
  * one work list, most expensive first.  Two knobs shape it: the work-list
  * granularity (tiles sized so that the list holds about `items_per_cu` items per
  * compute unit, unless tile_rot fixes the tile) and vote_parts (into how many work
- * units the vote splits each lane group's stream window: 32 or 64 reference
+ * units the vote splits each lane group's stream window: 16, 32 or 64 reference
  * points, chosen per problem as with dses_options.lane_group = 0, against the
  * window of x-sorted sources; the waves of a workgroup take units dynamically).
  * With DSES_BATCH_TUNE the call first times the sweep kernel alone on this batch

@@ -267,6 +267,33 @@ int choose_gref(const Geom &g, bool sorted, float x_extent, int asked)
     return 64.0f * x_extent <= 0.13f * (float)g.pps * (float)g.m ? 64 : 32;
 }
 
+// Smaller groups span less x, so their windows carry less slack (about group * X
+// source-bins per slab over all groups, X the reference's x extent in bins), but there
+// are more work units, each costing about kUnitSteps wave steps of set-up, padding and
+// slab-end imbalance (fitted); rho = n / (X + size_x) sources per bin turns a step into
+// 64 / rho source-bins.  The size with the least modelled cost wins (ties: the larger).
+// Box +-1 at a pitch of 0.01, ms a call with 16 / 32 / 64 points: 717 x
+// 1,024 points, 2,048 rotations 7.2 / 7.8 / 8.8; 2,000 x 4,096, 1,024 rotations 15.5 /
+// 13.4 / 13.9.
+int choose_group(const Geom &g, float x_extent, int asked, int vote_parts)
+{
+    constexpr float kUnitSteps = 4.9f;
+    if (asked) return asked;
+    const float per_unit = kUnitSteps * 64.0f * (x_extent + (float)g.size[0]) / (float)g.n;
+    int best = 0;
+    float least = 0.0f;
+    for (int group = 64; group >= 16; group >>= 1) {
+        const int groups = (g.m + group - 1) / group;
+        const int parts = vote_parts > 0 ? vote_parts : vote_parts_auto(groups);
+        const float cost = (float)group * x_extent + per_unit * (float)(groups * parts);
+        if (!best || cost < least) {
+            least = cost;
+            best = group;
+        }
+    }
+    return best;
+}
+
 // A workgroup holds a compute unit, so k rotations run in ceil(k / CUs) rounds and the
 // last may be nearly empty.  Items of fewer slabs fill it; each repeats the sort of the
 // sources, and the scores move to a launch of their own.  The estimate is the largest
@@ -801,6 +828,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     a.scratch_stride = job.n;
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
     a.gref = gref;
+    a.group = choose_group(g, ref_x_extent(ylo, yhi), o.lane_group, 0);
 
     HostGrid hg;                               // of a reference that is not resident
     if (scorer == DSES_SCORER_GRID) {

@@ -486,6 +486,12 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
     std::vector<SweepArgs> inst(b->cap_count);
     std::vector<StageDesc> stage(b->cap_count);
     std::vector<SelectDesc> sel(b->cap_count);
+    auto set_parts = [&](int i, int parts) {
+        const Prepared &x = P[i];
+        if (x.status != DSES_OK) return;
+        inst[i].vote_parts = parts;
+        inst[i].group = choose_group(x.g, ref_x_extent(x.ylo, x.yhi), 0, parts);
+    };
     uint32_t *status_dev = static_cast<uint32_t *>(b->status.ptr);
     DevResult *res_dev = static_cast<DevResult *>(b->results.ptr);
     for (int i = 0; i < count; ++i) {
@@ -529,7 +535,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         a.g = x.g;
         a.rec = reinterpret_cast<dses_record *>(arena + x.off_rec);
         a.k = x.k;
-        a.vote_parts = lay.vote_parts;
+        set_parts(i, lay.vote_parts);
         if (x.scorer == DSES_SCORER_GRID) {
             if (x.target) {
                 a.grid.pts = x.grid_pts;
@@ -598,7 +604,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
             build_items(L.items_per_cu, &items);
             header[0] = (int32_t)items.size() - n_general;
             header[2] = (int32_t)items.size();
-            for (int i = 0; i < count; ++i) inst[i].vote_parts = L.vote_parts;
+            for (int i = 0; i < count; ++i) set_parts(i, L.vote_parts);
             DSES_HIP(hipMemcpyAsync(b->items.ptr, items.data(), items.size() * sizeof(BatchItem),
                                     hipMemcpyHostToDevice, stream));
             DSES_HIP(hipMemcpyAsync(b->header.ptr, header, sizeof(header), hipMemcpyHostToDevice,
@@ -650,7 +656,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         n_items = (int)items.size();
         header[0] = n_items - n_general;
         header[2] = n_items;
-        for (int i = 0; i < count; ++i) inst[i].vote_parts = lay.vote_parts;
+        for (int i = 0; i < count; ++i) set_parts(i, lay.vote_parts);
         DSES_HIP(hipMemcpyAsync(b->items.ptr, items.data(), items.size() * sizeof(BatchItem),
                                 hipMemcpyHostToDevice, stream));
         DSES_HIP(hipMemcpyAsync(b->header.ptr, header, sizeof(header), hipMemcpyHostToDevice,

@@ -156,6 +156,9 @@ inline int choose_batch_gref(const Geom &g, bool sorted, float x_extent)
     const int gref = choose_gref(g, sorted, x_extent, 0);
     return gref != 0 && g.counter_bits == 32 ? 64 : gref;
 }
+// Reference points per lane group of the general path's vote with sorted sources: 16,
+// 32 or 64 (`asked` if not 0); vote_parts as in SweepArgs.
+int choose_group(const Geom &g, float x_extent, int asked, int vote_parts);
 // Staging of a reference of g.m points for a vote of geometry g with lane groups of
 // gref points (0: the general path), in bank order if `arrange`.
 // Items a rotation's slabs are split into by the plain path (1: none).

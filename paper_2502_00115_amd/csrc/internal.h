@@ -63,8 +63,8 @@ struct Field {
 // bin (16 when the reachable range fits).
 constexpr int kSrcBuckets = 8192;
 constexpr int kSortMax = 16384;         // largest source cloud that is bucket-sorted
-// Vote work units per 64-point lane group when not fixed by the caller: enough
-// units for every wave to take several (at most 8 per group).
+// The general path's vote work units per lane group when not fixed by the caller:
+// enough units for every wave to take several (at most 8 per group).
 __host__ __device__ inline int vote_parts_auto(int groups)
 {
     const int g = 64 / (groups > 0 ? groups : 1);
@@ -111,8 +111,10 @@ struct SweepArgs {
     Field field;
     dses_record *rec;      // one record per rotation index
     int32_t k;             // rotations
-    int32_t vote_parts;    // stream-window parts per lane group (0: vote_parts_auto)
+    int32_t vote_parts;    // stream-window parts per lane group (0: parts_log2, or
+                           // vote_parts_auto in the general path)
     int32_t gref;          // reference points per lane group: 32 or 64; 0: general path
+    int32_t group;         // the general path's with sorted sources: 16, 32 or 64
 };
 
 // Scratch slot of one workgroup (int32 words): rotated fixed-point sources sorted

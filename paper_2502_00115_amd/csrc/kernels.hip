@@ -835,13 +835,15 @@ __device__ __forceinline__ void src_window(const SweepArgs &a, __amdgpu_buffer_r
 // x0 + np) into the LDS counters: planes of any width, sources of any number.  Work
 // units are (lane group, part of the group's stream range), G parts per group; waves
 // take units one at a time from an LDS counter (cleared with the slab).
-//   sorted: a lane group is 64 consecutive points of the x-sorted reference, two per
-//           lane (points j and j + 32), held by both half waves; the stream is the
-//           window of the rotation's x-sorted sources, padded to a multiple of 4 and
-//           taken in blocks of 8 (half h takes 4h .. 4h + 3) plus a strided tail
+//   GROUP:  a lane group is that many (16, 32 or 64) consecutive points of the x-sorted
+//           reference, two per lane (points j and j + GROUP / 2), held by each of the
+//           wave's 128 / GROUP lane sub-groups; the stream is the window of the
+//           rotation's x-sorted sources, padded to a multiple of 4 and taken in blocks
+//           of 512 / GROUP (sub-group h takes 4h .. 4h + 3) plus a strided tail
 //           (vote_span_lanes);
-//   else:   lanes hold 64 rotated sources, the stream is the whole reference.
-template <int CW, bool SORTED, bool WIDE>
+//   0:      lanes hold 64 rotated sources, the stream is the whole reference.
+// GROUP is a constant because as a run-time value it cost 1.5% of the sweep.
+template <int CW, int GROUP, bool WIDE>
 __device__ __forceinline__ void vote_slab(const SweepArgs *args, int32_t *sp, int k, int x0,
                                           int np, uint32_t *hist)
 {
@@ -865,15 +867,14 @@ __device__ __forceinline__ void vote_slab(const SweepArgs *args, int32_t *sp, in
     const uint32_t xofs = (uint32_t)x0 << 16;
     const int m = g.m;
     uint32_t *ctr = hist + kHistWordsMax + kUnitCounter;
-    if (SORTED) {
-        constexpr int lg = 5;
-        const int gsz = 1 << lg;               // lanes per copy of the group
-        const int gref = 2 * gsz;              // reference points per group
-        const int B = 256 >> lg;
+    if (GROUP) {
+        constexpr int gref = GROUP ? GROUP : 64;   // reference points per group
+        constexpr int gsz = gref / 2;          // lanes per copy of the group
+        constexpr int B = 256 / gsz;
         const int ngr = (m + gref - 1) / gref;
         const int G = a.vote_parts > 0 ? a.vote_parts : vote_parts_auto(ngr);
         const int total = ngr * G;
-        const uint32_t hoff = 16u * (uint32_t)(lane >> lg);
+        const uint32_t hoff = 16u * (uint32_t)(lane / gsz);
         // part boundaries lo + B * (nb * p * gmul / 8192), nb the window's blocks:
         // nb <= kSortMax / 4 and p * gmul < 8192, so the product stays below 2^32
         const uint32_t gmul = 8192u / (uint32_t)G;
@@ -1633,16 +1634,18 @@ __device__ __forceinline__ void score_candidate(const SweepArgs *args, int k, in
 // vote's 16-bit strides, or sources too many to be sorted.
 template <int CW>
 __device__ __forceinline__ void vote_slab_any(const SweepArgs *args, int32_t *sp, int k, int x0,
-                                              int np, uint32_t *hist, bool wide)
+                                              int np, uint32_t *hist, bool wide, int group)
 {
-    if (wide) {
-        if (sp)
-            vote_slab<CW, true, true>(args, sp, k, x0, np, hist);
-        else
-            vote_slab<CW, false, true>(args, sp, k, x0, np, hist);
-    } else {
-        vote_slab<CW, false, false>(args, sp, k, x0, np, hist);
-    }
+    if (!wide)
+        vote_slab<CW, 0, false>(args, sp, k, x0, np, hist);
+    else if (!sp)
+        vote_slab<CW, 0, true>(args, sp, k, x0, np, hist);
+    else if (group == 16)
+        vote_slab<CW, 16, true>(args, sp, k, x0, np, hist);
+    else if (group == 32)
+        vote_slab<CW, 32, true>(args, sp, k, x0, np, hist);
+    else
+        vote_slab<CW, 64, true>(args, sp, k, x0, np, hist);
 }
 
 // Vote, mode and score one rotation k with the whole workgroup; sp is the
@@ -1679,7 +1682,7 @@ __device__ __forceinline__ void vote_mode(const SweepArgs *args, int k, uint32_t
         if (GREF)
             vote_windows<CW, GREF ? GREF : 64>(args, sp, x0, np, hist);
         else
-            vote_slab_any<CW>(args, sp, k, x0, np, hist, g.wide != 0);
+            vote_slab_any<CW>(args, sp, k, x0, np, hist, g.wide != 0, a.group);
         __syncthreads();
         SlabWords words;
         const uint32_t c = take_slab<CW>(hist, (int)((uint32_t)np * plane + 3) >> 2, words);

@@ -356,6 +356,7 @@ dses_status ServerImpl::prepare(Request *r)
     a.scratch_stride = r->n;                 // arrays inside the slice's fixed-size slots
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
     a.gref = gref;
+    a.group = choose_group(g, ref_x_extent(ylo, yhi), 0, 0);
     r->general = gref == 0;
     a.g = g;
     a.grid = cg;

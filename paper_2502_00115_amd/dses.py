@@ -308,7 +308,7 @@ def register(src, tgt, rotations, eps, metric="trunc_l2", *, delta_t=None, tau=N
     """dses_register: the full sweep over the rotation list (top_k > 0: also the best
     top_k candidates in selection order, Registration.top; q > 0: score only the
     rotations with M_k >= q M*; lp: exponent of metric "trunc_lp"; lane_group: vote
-    layout, 32 or 64 reference points per lane group (16: as 32), 0 automatic)."""
+    layout, 16, 32 or 64 reference points per lane group, 0 automatic)."""
     args = _Args()
     ps, n = args.ptr(src, 3)
     pt, m = args.ptr(tgt, 3)

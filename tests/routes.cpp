@@ -1,0 +1,29 @@
+// Which layout the library picks for a plain call: its own host rules, called directly.
+#include "host.h"
+
+using namespace dses;
+
+// box: translations in [-box, box]^3; out: counter bits, wide, nslabs, pps, sorted, gref,
+// group, arrange, parts.
+extern "C" int route(const float *tgt, int m, int n, int k, float eps, float box, int lane_group,
+                     int32_t *out)
+{
+    Params p;
+    const float lo[3] = {-box, -box, -box}, hi[3] = {box, box, box};
+    dses_status st = resolve_params(eps, DSES_TRUNC_L2, 0.0f, 0.0f, lo, hi, DSES_SCORER_AUTO, &p);
+    if (st != DSES_OK) return st;
+    Geom g;
+    const int bits = counter_bits_for(counter_bound(tgt, m, n, p), n, m, p);
+    if ((st = plan_geom(nullptr, p, n, m, bits, &g)) != DSES_OK) return st;
+    std::vector<int32_t> perm;
+    sort_by_x(tgt, m, &perm);
+    int32_t ylo = 0, yhi = 0;
+    const bool sorted = n <= kSortMax && ref_x_range(tgt, perm, p.delta, p.klo[0], &ylo, &yhi);
+    const float x = ref_x_extent(ylo, yhi);
+    const int gref = choose_gref(g, sorted, x, lane_group);
+    const int32_t v[9] = {bits, g.wide, g.nslabs, g.pps, sorted, gref,
+                          gref || !sorted ? 0 : choose_group(g, x, lane_group, 0),
+                          worth_arranging(g, gref, x, k), gref ? choose_parts(g, k, x, 256) : 1};
+    for (int i = 0; i < 9; ++i) out[i] = v[i];
+    return DSES_OK;
+}
