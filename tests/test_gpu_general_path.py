@@ -1,0 +1,117 @@
+"""The general vote path, for x planes wider than the windowed vote's 16-bit strides (more
+than 65,535 bytes of counters) and for sources too many to be sorted: both counter widths,
+every lane-group size, alone, in batches and served, at the sizes where its pieces end.
+Each test shows that its calls take the path (routes.py)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_00115_amd import synth
+from parity import check_selection, compare_records
+from routes import clouds, route
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2502_00115_amd import dses  # noqa: E402
+
+
+# n: below, at and past a tail step and a block (8, 16 and 32 sources with groups of 64, 32
+# and 16); m: the same for the groups; 420 reference points in one bin: 32-bit counters
+@pytest.mark.parametrize("n,m,eps,clustered", [
+    (3, 15, 0.01, 0), (4, 16, 0.01, 0), (5, 17, 0.01, 0), (7, 31, 0.01, 0), (9, 33, 0.01, 0),
+    (16, 63, 0.01, 0), (17, 65, 0.01, 0), (31, 129, 0.01, 0), (33, 200, 0.01, 0),
+    (150, 700, 0.01, 0), (1500, 300, 0.01, 0), (160, 600, 0.0125, 420), (157, 1025, 0.0125, 420),
+])
+def test_wide_planes_match_the_oracle(n, m, eps, clustered):
+    src, tgt, rot = clouds(n, m, 100 + n + m, clustered)
+    r = route(n, tgt, len(rot), eps)
+    assert r.wide and r.sorted and r.gref == 0 and r.bits == (32 if clustered else 16)
+    ref = oracle.records(src, tgt, rot, eps)
+    assert np.any(ref["valid"])
+    got = {}
+    for lg in (0, 16, 32, 64):
+        got[lg] = dses.register(src, tgt, rot, eps, records=True, lane_group=lg)
+        rep = compare_records(got[lg].records, ref, n, label=f"{n}x{m} lane_group={lg}")
+        check_selection(got[lg], rep, eps, label=f"{n}x{m} lane_group={lg}")
+    for lg in (16, 32, 64):
+        assert got[lg].records.tobytes() == got[0].records.tobytes()
+
+
+@pytest.mark.parametrize("m,eps,clustered,bits,wide", [
+    (3, 0.05, 0, 16, 0), (40, 0.05, 30, 32, 0), (3, 0.01, 0, 16, 1), (41, 0.0125, 30, 32, 1),
+])
+def test_unsorted_sources_match_the_oracle(m, eps, clustered, bits, wide):
+    n = 16385
+    src, tgt, rot = clouds(n, m, 7, clustered)
+    r = route(n, tgt, 3, eps)
+    assert (r.sorted, r.gref, r.bits, r.wide) == (0, 0, bits, wide)
+    ref = oracle.records(src, tgt, rot[:3], eps)
+    got = dses.register(src, tgt, rot[:3], eps, records=True)
+    compare_records(got.records, ref, n, label=f"m={m} eps={eps}")
+
+
+def _problems():
+    """Problems of both paths, the general ones with 16- and 32-bit counters and unsorted."""
+    out = []
+    for i, (n, m, eps, clustered) in enumerate([
+            (60, 300, 0.05, 0), (100, 350, 0.01, 0), (140, 400, 0.03, 0), (180, 450, 0.0125, 420),
+            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 420)]):
+        src, tgt, rot = clouds(n, m, 40 + i, clustered)
+        r = route(n, tgt, len(rot), eps)
+        assert (r.gref == 0) == (i in (1, 3, 4, 5)) and r.bits == (32 if clustered else r.bits)
+        out.append(dict(src=src, tgt=tgt, rotations=rot, eps=eps))
+    return out
+
+
+def _alone(p):
+    return dses.register(p["src"], p["tgt"], p["rotations"], p["eps"], records=True)
+
+
+def test_batch_mixes_both_paths():
+    """Every problem of a mixed batch returns what it returns alone, eagerly and by graph
+    replays, with windowed-only and general-only batches in between; any split of the windows."""
+    probs = _problems()
+    alone = [_alone(p).records.tobytes() for p in probs]
+    general = [1, 3, 4, 5]
+    windowed = [0, 2, 6]
+    every = list(range(len(probs)))
+    for which, graph in ((every, True), (every, False), (every, True), (windowed, True),
+                         (general, True), (every, True), (general, False)):
+        got, st = dses.register_batch([probs[i] for i in which], records=True, use_graph=graph)
+        assert st == [0] * len(which)
+        assert [g.records.tobytes() for g in got] == [alone[i] for i in which]
+    for parts in (1, 3, 16):
+        got, _ = dses.register_batch(probs, records=True, vote_parts=parts)
+        assert [g.records.tobytes() for g in got] == alone
+    got, _ = dses.register_batch(probs, records=True, autotune=True)
+    assert [g.records.tobytes() for g in got] == alone
+
+
+def test_server_mixes_both_paths():
+    """Served requests of both paths, all outstanding at once, equal their lone calls."""
+    _, tgt, _ = clouds(10, 900, 5)
+    rot = synth.random_rotations(np.random.default_rng(6), 300).reshape(-1, 9).astype(np.float32)
+    target, rotset = dses.Target(tgt), dses.RotationSet(rot)
+    reqs = []
+    for i in range(12):
+        n, eps = 70 + 45 * i, (0.01, 0.03, 0.0125)[i % 3]
+        src = clouds(n, 900, 5)[0]
+        assert (route(n, tgt, len(rot), eps).gref == 0) == (i % 3 == 0)
+        reqs.append((src, eps))
+    with_records = [i % 2 == 0 for i in range(12)]
+    want = [dses.register(src, tgt, rot, eps, records=True) for src, eps in reqs]
+    srv = dses.Server()
+    for _ in range(2):
+        ids = [srv.submit(target, rotset, src, eps, records=rec)
+               for (src, eps), rec in zip(reqs, with_records)]
+        for w, i, rec in zip(want, ids, with_records):
+            g = srv.wait(i, timeout_ms=60000)
+            assert (g.rot_index, g.error, g.inliers, g.votes) == (w.rot_index, w.error, w.inliers,
+                                                                  w.votes)
+            if rec:
+                assert g.records.tobytes() == w.records.tobytes()
+    srv.close()
