@@ -105,13 +105,14 @@ def test_server_mixes_both_paths():
     with_records = [i % 2 == 0 for i in range(12)]
     want = [dses.register(src, tgt, rot, eps, records=True) for src, eps in reqs]
     srv = dses.Server()
+    got = []
     for _ in range(2):
         ids = [srv.submit(target, rotset, src, eps, records=rec)
                for (src, eps), rec in zip(reqs, with_records)]
-        for w, i, rec in zip(want, ids, with_records):
-            g = srv.wait(i, timeout_ms=60000)
-            assert (g.rot_index, g.error, g.inliers, g.votes) == (w.rot_index, w.error, w.inliers,
-                                                                  w.votes)
-            if rec:
-                assert g.records.tobytes() == w.records.tobytes()
+        got += [srv.wait(i, timeout_ms=60000) for i in ids]
     srv.close()
+    for g, w, rec in zip(got, 2 * want, 2 * with_records):
+        assert (g.rot_index, g.error, g.inliers, g.votes) == (w.rot_index, w.error, w.inliers,
+                                                              w.votes)
+        if rec:
+            assert g.records.tobytes() == w.records.tobytes()
