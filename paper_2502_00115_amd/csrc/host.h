@@ -234,7 +234,8 @@ struct TargetRes {
     struct Stage {                           // staged copy for one (delta, box)
         float delta;
         int32_t klo[3];
-        int32_t zbits, gref, px, py;         // the layout it is staged for
+        int32_t zbits, gref;                 // the layout it is staged for
+        int32_t px, py;                      // the strides its bank order is made for
         int32_t *yq;                         // fixed-point copy (stage_words(m) int32)
         float *yt;
     };
@@ -307,7 +308,8 @@ int64_t target_block_population(TargetRes *tm, const Params &p);
 // be used.
 bool target_x_range(TargetRes *tm, const Params &p, int32_t *ylo, int32_t *yhi);
 // Stage a resident target for geometry g and lane groups of gref points (cached by
-// pitch, box and layout; holds tm->grid_mu while building; synchronous on `stream`).
+// pitch, box origin and layout, with bank orders for a few strides; holds tm->grid_mu
+// while building; synchronous on `stream`).
 dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, int gref,
                                 hipStream_t stream, const TargetRes::Stage **out);
 // Build (or reuse) the resident target's cell grid for radius r; fills cg.

@@ -88,12 +88,21 @@ dses_status ensure_target_stage(TargetRes *tm, const Params &p, const Geom &g, i
 {
     std::lock_guard<std::mutex> gl(tm->grid_mu);
     const StageDesc want = stage_desc(g, gref, gref != 0, nullptr, nullptr, nullptr, nullptr);
+    // Any copy of the pitch, origin, z width and group size gives the same records: only
+    // the bank order depends on the plane and row strides, so boxes that differ in their
+    // upper ends alone share copies once there are kStageOrders of them.
+    constexpr int kStageOrders = 4;
+    const TargetRes::Stage *hit = nullptr;
+    int orders = 0;
     for (const auto &st : tm->stages)
         if (st.delta == p.delta && st.klo[0] == p.klo[0] && st.klo[1] == p.klo[1] &&
-            st.klo[2] == p.klo[2] && st.zbits == want.zbits && st.gref == gref &&
-            st.px == want.px && st.py == want.py) {
-            *out = &st;
-            return DSES_OK;
+            st.klo[2] == p.klo[2] && st.zbits == want.zbits && st.gref == gref) {
+            const bool same = gref == 0 || (st.px == want.px && st.py == want.py);
+            if (same || !hit) hit = &st;
+            if (same || ++orders == kStageOrders) {
+                *out = hit;
+                return DSES_OK;
+            }
         }
     const size_t m = (size_t)tm->m;
     if (tm->perm_x.empty()) sort_by_x(tm->host_aos.data(), tm->m, &tm->perm_x);
