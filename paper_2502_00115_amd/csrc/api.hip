@@ -306,7 +306,8 @@ int choose_group(const Geom &g, float x_extent, int asked, int vote_parts)
 // Measured (ms, whole / in parts): 2,000 x 8,192 points at 0.03, 100 rotations 1.32 /
 // 0.82, 300 rotations 2.33 / 1.63, 576 rotations 3.15 / 2.50; 4,096 x 16,384 points 4.21 / 2.23,
 // 7.55 / 4.88, 10.77 / 8.23; 1,000 x 8,192 points at 0.05 (two slabs), 576 rotations 1.83 /
-// 1.98, so the rule leaves it whole.
+// 1.98, so the rule leaves it whole.  The estimate itself takes 9 us at 15
+// slabs and 13 at 84 (34 and 68 with a division per part, place and probe).
 int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu)
 {
     constexpr int kMostParts = 16, kProbes = 16;
@@ -318,37 +319,46 @@ int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu)
         return u < 0 ? 0.5 * (1 + u) * (1 + u) : 1 - 0.5 * (1 - u) * (1 - u);
     };
     const double pairs = (double)g.n * g.m / 8.5, sort = 8000.0 + 3.0 * g.n;
-    auto slab = [&](int s, double shift) {
-        const double x0 = s * g.pps - 0.5 * g.size[0] + shift;
-        return 8000.0 + pairs * (below(x0 + g.pps) - below(x0));
-    };
-    auto cost = [&](int parts, double shift) {
-        double item[kMostParts], most = 0;
-        for (int p = 0; p < parts; ++p) {
-            item[p] = sort;
-            for (int s = p; s < slabs; s += parts) item[p] += slab(s, shift);
+    std::vector<double> weight[3];                 // of the slabs, by the clouds' place
+    for (int side = 0; side < 3; ++side)
+        for (int s = 0; s < slabs; ++s) {
+            const double x0 = s * g.pps - 0.5 * g.size[0] + 0.25 * (side - 1) * g.size[0];
+            weight[side].push_back(8000.0 + pairs * (below(x0 + g.pps) - below(x0)));
         }
-        const int64_t all = (int64_t)k * parts;
-        for (int q = 0; q < kProbes; ++q) {        // workgroups q n_cu / 16
-            const int64_t b = (int64_t)q * n_cu / kProbes;
-            if (b >= all) break;
-            double sum = 0;
-            for (int p = 0; p < parts; ++p) {      // its items b, b + n_cu, ... of part p
-                auto upto = [&](int64_t e) { return e > b ? (e - b + n_cu - 1) / n_cu : 0; };
-                sum += item[p] * (double)(upto((int64_t)(p + 1) * k) - upto((int64_t)p * k));
+    // time[side]: the largest sum of a workgroup's items
+    auto estimate = [&](int parts, double *time) {
+        double item[3][kMostParts];
+        for (int side = 0; side < 3; ++side) {
+            time[side] = 0;
+            for (int p = 0; p < parts; ++p) {
+                item[side][p] = sort;
+                for (int s = p; s < slabs; s += parts) item[side][p] += weight[side][s];
             }
-            most = std::max(most, sum);
         }
-        return most + (parts > 1 ? 24000.0 : 0.0);
+        for (int q = 0; q < kProbes; ++q) {        // workgroups q n_cu / 16
+            const int b = q * n_cu / kProbes;
+            if (b >= k * parts) break;
+            double sum[3] = {0, 0, 0};
+            uint32_t before = 0;                   // its items b, b + n_cu, ... of earlier parts
+            for (int p = 0; p < parts; ++p) {
+                const int e = (p + 1) * k;
+                const uint32_t upto = e > b ? (uint32_t)(e - b + n_cu - 1) / (uint32_t)n_cu : 0;
+                for (int side = 0; side < 3; ++side)
+                    sum[side] += item[side][p] * (double)(upto - before);
+                before = upto;
+            }
+            for (int side = 0; side < 3; ++side) time[side] = std::max(time[side], sum[side]);
+        }
     };
+    double whole[3], split[3];
+    estimate(1, whole);
     double least = 0.92;
     int best = 1;
     for (int parts = 2; parts <= std::min(slabs, kMostParts); ++parts) {
+        estimate(parts, split);
         double share = 0;                          // of the time in one piece
-        for (int side = -1; side <= 1; ++side) {
-            const double shift = 0.25 * side * g.size[0];
-            share = std::max(share, cost(parts, shift) / cost(1, shift));
-        }
+        for (int side = 0; side < 3; ++side)
+            share = std::max(share, (split[side] + 24000.0) / whole[side]);
         if (share < least) {
             least = share;
             best = parts;

@@ -1,6 +1,8 @@
 // Which layout the library picks for a plain call: its own host rules, called directly.
 #include "host.h"
 
+#include <chrono>
+
 using namespace dses;
 
 // box: translations in [-box, box]^3; out: counter bits, wide, nslabs, pps, sorted, gref,
@@ -26,4 +28,30 @@ extern "C" int route(const float *tgt, int m, int n, int k, float eps, float box
                           worth_arranging(g, gref, x, k), gref ? choose_parts(g, k, x, 256) : 1};
     for (int i = 0; i < 9; ++i) out[i] = v[i];
     return DSES_OK;
+}
+
+// Least time in us, of many tries, of choose_parts over `slabs` slabs of three planes and of
+// the order by x of an m-point reference.
+extern "C" void parts_and_sort_us(const float *tgt, int m, int slabs, int k, double *parts,
+                                  double *sort)
+{
+    Geom g{};
+    g.n = 64;
+    g.m = 256;
+    g.pps = 3;
+    g.size[0] = 3 * slabs;
+    auto least = [](auto f) {
+        double best = 1e30;
+        for (int i = 0; i < 200; ++i) {
+            const auto t = std::chrono::steady_clock::now();
+            f();
+            const std::chrono::duration<double, std::micro> d = std::chrono::steady_clock::now() - t;
+            best = std::min(best, d.count());
+        }
+        return best;
+    };
+    int sum = 0;
+    std::vector<int32_t> perm;
+    *parts = least([&] { sum += choose_parts(g, k, 100.0f, 256); });
+    *sort = least([&] { sort_by_x(tgt, m, &perm); });
 }

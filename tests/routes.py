@@ -38,6 +38,13 @@ def route(n, tgt, k, eps, box=1.0, lane_group=0):
     return Route(*out)
 
 
+def parts_and_sort_us(tgt, slabs, k):
+    parts, sort = C.c_double(), C.c_double()
+    _lib().parts_and_sort_us(C.c_void_p(tgt.ctypes.data), len(tgt), slabs, k, C.byref(parts),
+                             C.byref(sort))
+    return parts.value, sort.value
+
+
 def clouds(n, m, seed, clustered=0):
     """A source cut from an m-point reference, moved and jittered, and five rotations;
     clustered: that many reference points lie within a tenth of a millimetre."""

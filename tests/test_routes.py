@@ -1,7 +1,7 @@
 """The host rules that pick the vote's layout (CPU only)."""
 import pytest
 
-from routes import clouds, route
+from routes import clouds, parts_and_sort_us, route
 
 
 # planes of 201 x 201 bins: small sources gain from small groups, whose windows carry less
@@ -14,3 +14,22 @@ def test_group_of_wide_planes(n, m, group):
     assert r.wide and r.sorted and r.gref == 0 and r.group == group
     for asked in (16, 32, 64):
         assert route(n, tgt, 1000, 0.01, lane_group=asked).group == asked
+
+
+# slabs of few rotations: parts taken at 1, 100, 257, 576 and 2,304 rotations
+@pytest.mark.parametrize("n,m,eps,parts", [
+    (500, 3000, 0.04, (2, 2, 1, 1, 1)), (500, 3000, 0.035, (3, 2, 3, 1, 1)),
+    (300, 8192, 0.03, (4, 2, 4, 4, 1)), (400, 3000, 0.0115, (16, 5, 9, 4, 1)),
+    (2600, 4097, 0.03, (8, 5, 7, 4, 1)), (900, 3000, 0.06, (1, 1, 1, 1, 1)),
+])
+def test_parts(n, m, eps, parts):
+    _, tgt, _ = clouds(n, m, 33)
+    assert tuple(route(n, tgt, k, eps).parts for k in (1, 100, 257, 576, 2304)) == parts
+
+
+def test_choosing_parts_is_short():
+    """Every call of up to 2,048 rotations over several slabs pays for the choice before its
+    first launch: less than half of what it pays to order 8,192 points (once as much)."""
+    _, tgt, _ = clouds(10, 8192, 1)
+    parts, sort = parts_and_sort_us(tgt, 84, 1000)
+    assert parts < 0.5 * sort
