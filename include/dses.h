@@ -161,9 +161,10 @@ typedef struct {
                                  4-source pieces of its window; 16 is taken as 32),
                                  or, for lattices with more than 65,535 bytes of
                                  counters in an x plane, 16, 32 or 64 (a wave holds
-                                 128 / lane_group copies); 0 -> chosen per call from
-                                 the sizes and the reference's extent.  Results do
-                                 not depend on it; other values are DSES_E_INVAL      */
+                                 128 / lane_group copies); 0 -> either vote and its
+                                 group chosen per call from the sizes and the
+                                 reference's extent and density.  Results do not
+                                 depend on it; other values are DSES_E_INVAL          */
     int32_t df_lookup;        /* dses_df_lookup of the DF scorer; 0 -> NEAREST         */
 } dses_options;
 
@@ -361,10 +362,10 @@ typedef struct {
     int32_t tile_rot;         /* rotations per work item; 0 -> tuned or default layout */
     int32_t vote_parts;       /* vote work units per lane group (parts of its
                                  stream window, 1..16, rounded down to a power of
-                                 two but on the wide planes and unsorted sources of
-                                 the general vote); 0 -> tuned or automatic (about
-                                 96 units per slab, 64 in the general vote, at most
-                                 8 parts, per problem)                              */
+                                 two but for problems that take the general vote);
+                                 0 -> tuned or automatic (about 96 units per slab, no
+                                 part shorter than about 16 sources; 64 in the general
+                                 vote; at most 8 parts, per problem)                */
     void *stream;
     int32_t df_lookup;        /* dses_df_lookup for DF-scored problems; 0 -> NEAREST  */
 } dses_batch_opts;

@@ -254,17 +254,78 @@ dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, i
     return DSES_OK;
 }
 
-// A group's windows cover its own x extent besides the slab's planes, and 64 points
-// span twice the extent of 32 but need half the set-ups and half the loads.  Measured
-// with both (us per rotation, 32 / 64 points): where 64 points span 0.08-0.11 of the
-// slab's planes 1,269 / 1,197 (2,000 x 8,192), 159 / 157 (1,000 x 2,000), 448 / 427
-// (2,000 x 3,000); at 0.14-0.2 of them 78 / 80 (500 x 1,500), 77 / 79 (717 x 1,024),
-// 46 / 48 (300 x 1,000); at 0.4 62 / 68 (1,000 x 500), 265 / 296 (1,500 x 1,500).
-int choose_gref(const Geom &g, bool sorted, float x_extent, int asked)
+// Parts of a lane group's windows in the windowed vote, a power of two: `asked` rounded
+// down, or about kVoteUnits units per slab for the 16 waves, at most 8, with no part
+// shorter than a block of 16 sources on average but for two units a wave.  Halving the
+// parts of shorter ones took 0.78 to 0.93 of the time (100 x 3,000 points at 0.0118 2.37 /
+// 1.86 us a rotation, 400 x 1,000 2.13 / 1.88), of parts of 20 to 300 sources 1.0 to 1.18
+// (1,500 x 2,000 at 0.015 4.07 / 4.36, 4,000 x 1,000 2.41 / 2.74).
+int window_parts(const Geom &g, int gref, float x_extent, int asked)
 {
-    if (!sorted || g.wide) return 0;
-    if (asked) return asked > 32 ? 64 : 32;
-    return 64.0f * x_extent <= 0.13f * (float)g.pps * (float)g.m ? 64 : 32;
+    constexpr int kVoteUnits = 96;
+    int parts = 1;
+    if (asked > 0) {
+        while (parts < 16 && 2 * parts <= asked) parts *= 2;
+        return parts;
+    }
+    const int groups = (g.m + gref - 1) / gref;
+    const double window = (g.pps + (double)gref * x_extent / g.m) * g.n / (x_extent + g.size[0]);
+    while (parts < 8 && groups * 2 * parts <= kVoteUnits &&
+           (window >= 2 * parts * 16 || groups * 2 * parts <= 32))
+        parts *= 2;
+    return parts;
+}
+
+// Costs per slab, in pairs of a 32-point group.  A group's windows cover its own x extent
+// besides the slab's planes, so larger groups stream more sources, but they are fewer
+// and need half the loads per pair; a unit's set-up is worth kUnit pairs.  64 points are
+// taken only where every wave gets a group (1,500 x 300 points 0.25 / 0.28 us).  The
+// general path pays more for a pair and a unit, but it has groups of 16 points, which
+// matter where even 32 span more than a slab, and whose pairs meet less often in one
+// counter where a few lattice cells hold much of the reference.  The share of the pairs
+// that lie in the box in x is that of two clouds of the reference's extent about its
+// middle.  Constants fitted to 450 sizes and lattices; us a rotation, groups of 32 / 64 /
+// general path: 2,000 x 8,192 at 0.03 3.66 / 3.48 / 5.00; 717 x 1,024 0.30 / 0.31 / 0.32;
+// 200 x 17,555 at 0.0118 9.6 / 6.9 / 6.5; 12,000 x 100 8.1 / 14.5 / 5.7; 4,000 x 1,000 4.5 /
+// 6.4 / 4.0; 5,298 x 853 at 0.046, a third of them in one cell, 2.7 / 2.7 / 2.0.
+VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t population, int asked,
+                         bool batched)
+{
+    constexpr double kUnit = 300.0, kLarge = 0.95, kGeneralUnit = 600.0, kGeneral = 1.1;
+    VoteLayout l{0, 64, 0, 0.0};
+    if (!sorted) return l;
+    l.group = choose_group(g, x_extent, asked, 0);
+    if (g.wide) return l;
+    const double m = g.m, X = x_extent;
+    const double u = std::min(1.0, g.size[0] / (2.0 * X));
+    const double pairs = (double)g.n * m * u * (2.0 - u) / g.nslabs;
+    auto reach = [&](int group) { return 1.0 + group * X / (m * g.pps); };
+    // the part of the reference in the fullest block of cells, beyond what a surface has
+    // there and one set of lanes
+    const double full = std::max(0.0, (double)(population - 16) / m - 8.0 / (X * X));
+    double cost[2];
+    for (int i = 0; i < 2; ++i) {
+        const int gref = 32 << i, groups = (g.m + gref - 1) / gref;
+        cost[i] = kUnit * groups * window_parts(g, gref, x_extent, 0) +
+                  pairs * (groups * gref / m) * reach(gref) * (i ? kLarge : 1.0) * (1.0 + 5.0 * full);
+    }
+    const bool large = asked ? asked > 32 : (batched && g.counter_bits == 32) ||
+                                              (g.m > 15 * 64 && cost[1] < cost[0]);
+    l.gref = large ? 64 : 32;
+    l.parts = window_parts(g, l.gref, x_extent, 0);
+    l.general = HUGE_VAL;
+    if (asked) return l;
+    const int groups = (g.m + 15) / 16;
+    const double general = kGeneralUnit * groups * vote_parts_auto(groups) +
+                           kGeneral * pairs * (groups * 16 / m) * reach(16) * (1.0 + 2.2 * full);
+    l.group = 16;
+    l.general = general / cost[large];
+    // windows of a few sources over many groups: the general path's units are cheaper
+    if (large && g.m > 64 * 64 && (g.pps + 64 * X / m) * g.n / (X + g.size[0]) < 4.0) {
+        l.group = 64;
+        l.general = std::min(l.general, 0.94);
+    }
+    return l;
 }
 
 // Smaller groups span less x, so their windows carry less slack (about group * X
@@ -306,10 +367,11 @@ int choose_group(const Geom &g, float x_extent, int asked, int vote_parts)
 // Measured (ms, whole / in parts): 2,000 x 8,192 points at 0.03, 100 rotations 1.32 /
 // 0.82, 300 rotations 2.33 / 1.63, 576 rotations 3.15 / 2.50; 4,096 x 16,384 points 4.21 / 2.23,
 // 7.55 / 4.88, 10.77 / 8.23; 1,000 x 8,192 points at 0.05 (two slabs), 576 rotations 1.83 /
-// 1.98, so the rule leaves it whole.  The estimate itself takes 9 us at 15
-// slabs and 13 at 84 (34 and 68 with a division per part, place and probe).
-int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu)
+// 1.98, so the rule leaves it whole.  The estimate itself takes 9 us at 15 slabs and 13 at
+// 84 (34 and 68 with a division per part, place and probe).
+int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu, double *share)
 {
+    *share = 1.0;
     constexpr int kMostParts = 16, kProbes = 16;
     const int slabs = (g.size[0] + g.pps - 1) / g.pps;
     if (slabs < 2 || k > 8 * n_cu) return 1;       // at most one round of nine to gain
@@ -356,11 +418,11 @@ int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu)
     int best = 1;
     for (int parts = 2; parts <= std::min(slabs, kMostParts); ++parts) {
         estimate(parts, split);
-        double share = 0;                          // of the time in one piece
+        double time = 0;                           // as a share of the time in one piece
         for (int side = 0; side < 3; ++side)
-            share = std::max(share, (split[side] + 24000.0) / whole[side]);
-        if (share < least) {
-            least = share;
+            time = std::max(time, (split[side] + 24000.0) / whole[side]);
+        if (time < least) {
+            *share = least = time;
             best = parts;
         }
     }
@@ -781,10 +843,10 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
             }
         ht = host_copy.data();
     }
-    const int64_t bound =
-        job.target ? target_block_population(const_cast<TargetRes *>(job.target), p) * job.n
-                   : counter_bound(ht, job.m, job.n, p);
-    const int counter_bits = counter_bits_for(bound, job.n, job.m, p);
+    const int64_t population = job.target
+                                   ? target_block_population(const_cast<TargetRes *>(job.target), p)
+                                   : ref_block_population(ht, job.m, p);
+    const int counter_bits = counter_bits_for(population * job.n, job.n, job.m, p);
     Geom g;
     if ((st = plan_geom(c, p, job.n, job.m, counter_bits, &g)) != DSES_OK) return st;
 
@@ -804,10 +866,19 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     }
     int32_t ylo = 0, yhi = 0;
     const bool sorted = job.n <= kSortMax && ref_x_range(ht, *perm, p.delta, p.klo[0], &ylo, &yhi);
-    const int gref = choose_gref(g, sorted, ref_x_extent(ylo, yhi), o.lane_group);
-    const int parts = gref && !arena && !job.exhaustive && !(o.q > 0.0f)
-                          ? choose_parts(g, job.k, ref_x_extent(ylo, yhi), c->n_cu)
-                          : 1;
+    const float x_extent = ref_x_extent(ylo, yhi);
+    VoteLayout lay{};                          // Alg. 1 takes no votes
+    if (!job.exhaustive)
+        lay = choose_layout(g, sorted, x_extent, population, o.lane_group, false);
+    double share = 1.0;                        // of its time that a split leaves the windowed vote
+    int parts = lay.gref && !arena && !(o.q > 0.0f)
+                    ? choose_parts(g, job.k, x_extent, c->n_cu, &share)
+                    : 1;
+    if (lay.general < share) {
+        lay.gref = 0;
+        lay.parts = 0;
+        parts = 1;
+    }
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)job.k * parts, c->n_cu));
     void *d_perm = nullptr, *d_scratch = nullptr, *d_yq = nullptr, *d_yt = nullptr;
     void *d_rec = nullptr, *d_status = nullptr;
@@ -837,8 +908,9 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     a.scratch = sorted ? static_cast<int32_t *>(d_scratch) : nullptr;
     a.scratch_stride = job.n;
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-    a.gref = gref;
-    a.group = choose_group(g, ref_x_extent(ylo, yhi), o.lane_group, 0);
+    a.gref = lay.gref;
+    a.group = lay.group;
+    a.vote_parts = lay.parts;
 
     HostGrid hg;                               // of a reference that is not resident
     if (scorer == DSES_SCORER_GRID) {
@@ -917,7 +989,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     prepare.end();
     TraceRange device("dses.sweep_select");    // launches to the result on the host
     rec_ev(0);
-    const bool arrange = worth_arranging(g, a.gref, ref_x_extent(ylo, yhi), job.k);
+    const bool arrange = worth_arranging(g, a.gref, x_extent, job.k);
     const CheckArgs ca{job.src,  job.n, job.tgt, job.m, job.rot, job.k, kSrcCoordLimit,
                        ref_coord_limit(p), bad};
     DSES_HIP(launch_prepare(check_inputs ? &ca : nullptr,

@@ -42,6 +42,7 @@ struct Prepared {
     const std::vector<int32_t> *perm = nullptr;
     int32_t ylo = 0, yhi = 0;              // ref_x_range of the sorted reference
     bool sorted = false;
+    int64_t population = 0;                // ref_block_population
     HostGrid grid;                          // GRID scorer (non-resident targets)
     const float *grid_pts = nullptr;        // device (resident cache)
     const int32_t *grid_start = nullptr;
@@ -83,7 +84,7 @@ BatchState *g_batch = nullptr;
 // 3.26 / 3.20).
 struct Layout {
     int items_per_cu = 96;
-    int vote_parts = 0;                // 0: vote_parts_auto
+    int vote_parts = 0;                // 0: by the problem's sizes
 };
 
 // Tuned layouts by batch class (count, scorer, log2 buckets of total pairs, mean
@@ -320,9 +321,9 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
             return;
         }
         x.host_tgt = ht;
-        const int64_t bound = T ? target_block_population(const_cast<TargetRes *>(T), x.p) * x.n
-                                : counter_bound(ht, x.m, x.n, x.p);
-        const int bits = counter_bits_for(bound, x.n, x.m, x.p);
+        x.population = T ? target_block_population(const_cast<TargetRes *>(T), x.p)
+                         : ref_block_population(ht, x.m, x.p);
+        const int bits = counter_bits_for(x.population * x.n, x.n, x.m, x.p);
         if ((st = plan_geom(c, x.p, x.n, x.m, bits, &x.g)) != DSES_OK) { x.status = st; return; }
         if (T) {
             auto *tm = const_cast<TargetRes *>(T);
@@ -420,10 +421,11 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
     // (the general path's tiles, which a launch of their own runs, at the end of the
     // list); n_general is their number
     int n_general = 0;
-    std::vector<int32_t> gref(count, 0);
+    std::vector<VoteLayout> vote(count);
     for (int i = 0; i < count; ++i)
         if (P[i].status == DSES_OK)
-            gref[i] = choose_batch_gref(P[i].g, P[i].sorted, ref_x_extent(P[i].ylo, P[i].yhi));
+            vote[i] = choose_layout(P[i].g, P[i].sorted, ref_x_extent(P[i].ylo, P[i].yhi),
+                                    P[i].population, 0, true);
     auto build_items = [&](int items_per_cu, std::vector<BatchItem> *list) {
         const double target_cost = std::max(1.0, total / ((double)grid * items_per_cu));
         struct Tile { bool general; double cost; BatchItem it; };
@@ -438,8 +440,8 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                                  : (int)std::max(1.0, std::min((double)x.k, target_cost / per_rot));
             for (int32_t k0 = 0; k0 < x.k; k0 += tile) {
                 const int32_t k1 = std::min<int32_t>(x.k, k0 + tile);
-                tiles.push_back({gref[i] == 0, per_rot * (k1 - k0), BatchItem{i, k0, k1, 0}});
-                n_general += gref[i] == 0;
+                tiles.push_back({vote[i].gref == 0, per_rot * (k1 - k0), BatchItem{i, k0, k1, 0}});
+                n_general += vote[i].gref == 0;
             }
         }
         std::stable_sort(tiles.begin(), tiles.end(),
@@ -489,8 +491,9 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
     auto set_parts = [&](int i, int parts) {
         const Prepared &x = P[i];
         if (x.status != DSES_OK) return;
-        inst[i].vote_parts = parts;
-        inst[i].group = choose_group(x.g, ref_x_extent(x.ylo, x.yhi), 0, parts);
+        const float X = ref_x_extent(x.ylo, x.yhi);
+        inst[i].vote_parts = vote[i].gref ? window_parts(x.g, vote[i].gref, X, parts) : parts;
+        inst[i].group = x.g.wide ? choose_group(x.g, X, 0, parts) : vote[i].group;
     };
     uint32_t *status_dev = static_cast<uint32_t *>(b->status.ptr);
     DevResult *res_dev = static_cast<DevResult *>(b->results.ptr);
@@ -531,7 +534,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
         a.scratch = x.sorted ? static_cast<int32_t *>(b->scratch.ptr) : nullptr;
         a.scratch_stride = max_n;
         source_buckets(x.ylo, x.yhi, x.g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-        a.gref = gref[i];
+        a.gref = vote[i].gref;
         a.g = x.g;
         a.rec = reinterpret_cast<dses_record *>(arena + x.off_rec);
         a.k = x.k;

@@ -145,24 +145,31 @@ constexpr float kSrcCoordLimit = 1.0e4f;
 int counter_bits_for(int64_t bound, int32_t n, int32_t m, const Params &p);
 dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, int counter_bits,
                       Geom *g);
-// Reference points per lane group of the windowed vote (32 or 64; `asked` if not 0,
-// 16 taken as 32), or 0 where only the general path applies: sources not sorted, or
-// x planes wider than its 16-bit strides.
-int choose_gref(const Geom &g, bool sorted, float x_extent, int asked);
-// The same for the batched kernels, which hold fewer of the layouts: groups of 32 or 64
-// points under 16-bit counters, of 64 under 32-bit ones.
-inline int choose_batch_gref(const Geom &g, bool sorted, float x_extent)
-{
-    const int gref = choose_gref(g, sorted, x_extent, 0);
-    return gref != 0 && g.counter_bits == 32 ? 64 : gref;
-}
+// How a call votes.  gref: reference points per lane group of the windowed vote (32 or
+// 64; 16 asked for is taken as 32), 0 where only the general path applies (sources not
+// sorted, or x planes wider than 16-bit strides).  group: the general path's.  parts: a
+// group's windows are split into (0: vote_parts_auto of the general path).  general: the
+// general path's estimated time as a multiple of the windowed vote's.
+struct VoteLayout {
+    int gref, group, parts;
+    double general;
+};
+// population: ref_block_population; asked: the caller's lane_group.  batched: the
+// batched kernels hold groups of 32 or 64 points under 16-bit counters and of 64 under
+// 32-bit ones.  The plain path compares `general` with the share that choose_parts leaves.
+VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t population, int asked,
+                         bool batched);
+// Parts of a lane group's windows in the windowed vote, a power of two; asked: the
+// caller's vote_parts if not 0.
+int window_parts(const Geom &g, int gref, float x_extent, int asked);
 // Reference points per lane group of the general path's vote with sorted sources: 16,
 // 32 or 64 (`asked` if not 0); vote_parts as in SweepArgs.
 int choose_group(const Geom &g, float x_extent, int asked, int vote_parts);
+// Items a rotation's slabs are split into by the plain path (1: none); *share: the
+// estimated time as a share of that of whole rotations.
+int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu, double *share);
 // Staging of a reference of g.m points for a vote of geometry g with lane groups of
 // gref points (0: the general path), in bank order if `arrange`.
-// Items a rotation's slabs are split into by the plain path (1: none).
-int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu);
 StageDesc stage_desc(const Geom &g, int gref, bool arrange, const float *tgt, const int32_t *perm,
                      int32_t *yq, float *yt);
 // Whether a call of k rotations gains from bank order (k_arrange takes 20 us for

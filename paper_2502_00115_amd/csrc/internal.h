@@ -70,19 +70,6 @@ __host__ __device__ inline int vote_parts_auto(int groups)
     const int g = 64 / (groups > 0 ? groups : 1);
     return g < 1 ? 1 : (g > 8 ? 8 : g);
 }
-// The windowed vote's parts per lane group, as a power of two: `asked` rounded down,
-// or about kVoteUnits units per slab for the 16 waves (at most 8 parts).
-constexpr int kVoteUnits = 96;
-__host__ __device__ inline int parts_log2(int groups, int asked)
-{
-    int l = 0;
-    if (asked > 0) {
-        while (l < 4 && (2 << l) <= asked) ++l;
-        return l;
-    }
-    while (l < 3 && (groups << (l + 1)) <= kVoteUnits) ++l;
-    return l;
-}
 constexpr int kUnitCounter = 128;       // LDS scratch word: next vote work unit
 constexpr int kSrcBmin = 129;           // LDS scratch words: lowest and highest occupied
 constexpr int kSrcBmax = 130;           // source bucket of the current rotation
@@ -111,8 +98,8 @@ struct SweepArgs {
     Field field;
     dses_record *rec;      // one record per rotation index
     int32_t k;             // rotations
-    int32_t vote_parts;    // stream-window parts per lane group (0: parts_log2, or
-                           // vote_parts_auto in the general path)
+    int32_t vote_parts;    // stream-window parts per lane group: a power of two (window_parts),
+                           // or any number in the general path (0: vote_parts_auto)
     int32_t gref;          // reference points per lane group: 32 or 64; 0: general path
     int32_t group;         // the general path's with sorted sources: 16, 32 or 64
 };

@@ -1098,7 +1098,7 @@ __device__ __forceinline__ void vote_windows(const SweepArgs *args, int32_t *sp,
     const uint32_t hoff = 16u * (uint32_t)S::sub(lane), hoff2 = 2u * hoff;
     const int pt = S::point(lane);
 
-    const int lgp = parts_log2(ngr, a.vote_parts);
+    const int lgp = 31 - __builtin_clz((uint32_t)a.vote_parts);
     const int units = ngr << lgp;
     uint32_t *ctr = hist + kHistWordsMax + kUnitCounter;
     Windows w = group_windows(a, gxs, trs, 0, ngr, bmin, bmax, xofs, np, ns);
@@ -1636,7 +1636,7 @@ template <int CW>
 __device__ __forceinline__ void vote_slab_any(const SweepArgs *args, int32_t *sp, int k, int x0,
                                               int np, uint32_t *hist, bool wide, int group)
 {
-    if (!wide)
+    if (!sp && !wide)
         vote_slab<CW, 0, false>(args, sp, k, x0, np, hist);
     else if (!sp)
         vote_slab<CW, 0, true>(args, sp, k, x0, np, hist);
@@ -1837,7 +1837,8 @@ hipError_t launch_sweep_parts(const SweepArgs &a, int scorer, int grid, void *mo
                               hipStream_t stream)
 {
     if (a.k <= 0) return hipSuccess;
-    if (!a.scratch || !a.gref || parts < 1 || parts > a.g.nslabs) return hipErrorInvalidValue;
+    if (!a.scratch || !a.gref || a.vote_parts < 1 || parts < 1 || parts > a.g.nslabs)
+        return hipErrorInvalidValue;
     return a.g.counter_bits == 16
                ? launch_parts<16>(a, scorer, grid, static_cast<uint2 *>(modes), parts, stream)
                : launch_parts<32>(a, scorer, grid, static_cast<uint2 *>(modes), parts, stream);
@@ -1876,6 +1877,7 @@ static hipError_t launch_width(const SweepArgs &a, int scorer, int grid, hipStre
 hipError_t launch_sweep(const SweepArgs &a, int scorer, int grid, hipStream_t stream)
 {
     if (a.k <= 0) return hipSuccess;
+    if (a.gref && a.vote_parts < 1) return hipErrorInvalidValue;
     if (grid > a.k) grid = a.k;
     return a.g.counter_bits == 16 ? launch_width<16>(a, scorer, grid, stream)
                                   : launch_width<32>(a, scorer, grid, stream);

@@ -321,15 +321,16 @@ ServerImpl::~ServerImpl()
 dses_status ServerImpl::prepare(Request *r)
 {
     auto *tm = const_cast<TargetRes *>(r->target);
-    const int bits = counter_bits_for(target_block_population(tm, r->p) * r->n, r->n, r->m, r->p);
+    const int64_t population = target_block_population(tm, r->p);
+    const int bits = counter_bits_for(population * r->n, r->n, r->m, r->p);
     Geom g;
     dses_status st = plan_geom(c, r->p, r->n, r->m, bits, &g);
     if (st != DSES_OK) return st;
     const TargetRes::Stage *stg = nullptr;
     int32_t ylo = 0, yhi = 0;
     const bool sorted = r->n <= kSortMax && target_x_range(tm, r->p, &ylo, &yhi);
-    const int gref = choose_batch_gref(g, sorted, ref_x_extent(ylo, yhi));
-    if ((st = ensure_target_stage(tm, r->p, g, gref, up, &stg)) != DSES_OK) return st;
+    const VoteLayout lay = choose_layout(g, sorted, ref_x_extent(ylo, yhi), population, 0, true);
+    if ((st = ensure_target_stage(tm, r->p, g, lay.gref, up, &stg)) != DSES_OK) return st;
     CellGrid cg{};
     if (r->scorer == DSES_SCORER_GRID && (st = ensure_target_grid(tm, r->p.r, &cg)) != DSES_OK)
         return st;
@@ -355,9 +356,10 @@ dses_status ServerImpl::prepare(Request *r)
     a.scratch = sorted ? reinterpret_cast<int32_t *>(4) : nullptr;   // per-slice scratch at launch
     a.scratch_stride = r->n;                 // arrays inside the slice's fixed-size slots
     source_buckets(ylo, yhi, g.size[0], &a.sb_lo, &a.sb_shift, &a.sb_n);
-    a.gref = gref;
-    a.group = choose_group(g, ref_x_extent(ylo, yhi), 0, 0);
-    r->general = gref == 0;
+    a.gref = lay.gref;
+    a.group = lay.group;
+    a.vote_parts = lay.parts;
+    r->general = lay.gref == 0;
     a.g = g;
     a.grid = cg;
     if (r->scorer == DSES_SCORER_DF) {

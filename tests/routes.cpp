@@ -1,4 +1,5 @@
-// Which layout the library picks for a plain call: its own host rules, called directly.
+// Which layout the library picks for a plain call or a problem of a batch: its own host
+// rules, called directly.
 #include "host.h"
 
 #include <chrono>
@@ -6,27 +7,34 @@
 using namespace dses;
 
 // box: translations in [-box, box]^3; out: counter bits, wide, nslabs, pps, sorted, gref,
-// group, arrange, parts.
+// group, windows, arrange, parts.
 extern "C" int route(const float *tgt, int m, int n, int k, float eps, float box, int lane_group,
-                     int32_t *out)
+                     int batched, int32_t *out)
 {
     Params p;
     const float lo[3] = {-box, -box, -box}, hi[3] = {box, box, box};
     dses_status st = resolve_params(eps, DSES_TRUNC_L2, 0.0f, 0.0f, lo, hi, DSES_SCORER_AUTO, &p);
     if (st != DSES_OK) return st;
     Geom g;
-    const int bits = counter_bits_for(counter_bound(tgt, m, n, p), n, m, p);
+    const int64_t population = ref_block_population(tgt, m, p);
+    const int bits = counter_bits_for(population * n, n, m, p);
     if ((st = plan_geom(nullptr, p, n, m, bits, &g)) != DSES_OK) return st;
     std::vector<int32_t> perm;
     sort_by_x(tgt, m, &perm);
     int32_t ylo = 0, yhi = 0;
     const bool sorted = n <= kSortMax && ref_x_range(tgt, perm, p.delta, p.klo[0], &ylo, &yhi);
     const float x = ref_x_extent(ylo, yhi);
-    const int gref = choose_gref(g, sorted, x, lane_group);
-    const int32_t v[9] = {bits, g.wide, g.nslabs, g.pps, sorted, gref,
-                          gref || !sorted ? 0 : choose_group(g, x, lane_group, 0),
-                          worth_arranging(g, gref, x, k), gref ? choose_parts(g, k, x, 256) : 1};
-    for (int i = 0; i < 9; ++i) out[i] = v[i];
+    VoteLayout l = choose_layout(g, sorted, x, population, lane_group, batched);
+    double share = 1.0;
+    int parts = l.gref && !batched ? choose_parts(g, k, x, 256, &share) : 1;
+    if (!batched && l.general < share) {
+        l.gref = l.parts = 0;
+        parts = 1;
+    }
+    const int32_t v[10] = {bits, g.wide, g.nslabs, g.pps, sorted, l.gref,
+                           l.gref || !sorted ? 0 : l.group, l.parts,
+                           worth_arranging(g, l.gref, x, k), parts};
+    for (int i = 0; i < 10; ++i) out[i] = v[i];
     return DSES_OK;
 }
 
@@ -52,6 +60,7 @@ extern "C" void parts_and_sort_us(const float *tgt, int m, int slabs, int k, dou
     };
     int sum = 0;
     std::vector<int32_t> perm;
-    *parts = least([&] { sum += choose_parts(g, k, 100.0f, 256); });
+    double share;
+    *parts = least([&] { sum += choose_parts(g, k, 100.0f, 256, &share); });
     *sort = least([&] { sort_by_x(tgt, m, &perm); });
 }

@@ -14,7 +14,8 @@ from paper_2502_00115_amd import dses, synth
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-Route = namedtuple("Route", "bits wide nslabs pps sorted gref group arrange parts")
+# windows: parts of a lane group's windows; parts: of a rotation's slabs
+Route = namedtuple("Route", "bits wide nslabs pps sorted gref group windows arrange parts")
 
 
 @functools.lru_cache(maxsize=None)
@@ -29,11 +30,11 @@ def _lib():
     return C.CDLL(out)
 
 
-def route(n, tgt, k, eps, box=1.0, lane_group=0):
+def route(n, tgt, k, eps, box=1.0, lane_group=0, batched=False):
     tgt = np.ascontiguousarray(tgt, np.float32)
-    out = (C.c_int32 * 9)()
+    out = (C.c_int32 * 10)()
     st = _lib().route(C.c_void_p(tgt.ctypes.data), len(tgt), n, k, C.c_float(eps),
-                      C.c_float(box), lane_group, out)
+                      C.c_float(box), lane_group, int(batched), out)
     assert st == 0, st
     return Route(*out)
 

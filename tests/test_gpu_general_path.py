@@ -1,7 +1,7 @@
 """The general vote path, for x planes wider than the windowed vote's 16-bit strides (more
-than 65,535 bytes of counters) and for sources too many to be sorted: both counter widths,
-every lane-group size, alone, in batches and served, at the sizes where its pieces end.
-Each test shows that its calls take the path (routes.py)."""
+than 65,535 bytes of counters), for sources too many to be sorted and where it is the faster:
+both counter widths, every lane-group size, alone, in batches and served, at the sizes where
+its pieces end.  Each test shows that its calls take the path (routes.py)."""
 import numpy as np
 import pytest
 
@@ -54,14 +54,34 @@ def test_unsorted_sources_match_the_oracle(m, eps, clustered, bits, wide):
     compare_records(got.records, ref, n, label=f"m={m} eps={eps}")
 
 
+# groups of 16 points and of 64, whole and partial, one and many slabs, both counter widths
+@pytest.mark.parametrize("n,m,eps,clustered,group,bits", [
+    (12000, 100, 0.0118, 0, 16, 16), (3000, 17, 0.02, 0, 16, 16), (4000, 1001, 0.0118, 0, 16, 16),
+    (1000, 853, 0.0461, 285, 16, 32), (717, 1025, 0.03, 500, 16, 32),
+    (100, 5001, 0.0118, 0, 64, 16), (10, 8192, 0.03, 0, 64, 16),
+])
+def test_faster_general_path_equals_the_windowed_vote(n, m, eps, clustered, group, bits):
+    src, tgt, rot = clouds(n, m, 60 + m, clustered)
+    r = route(n, tgt, 2304, eps)
+    assert (r.wide, r.gref, r.group, r.bits) == (0, 0, group, bits)
+    more = synth.random_rotations(np.random.default_rng(m), 2304).reshape(-1, 9)
+    rot = np.concatenate([rot, more[len(rot):]]).astype(np.float32)
+    got = dses.register(src, tgt, rot, eps, records=True)
+    for lg in (32, 64):
+        assert route(n, tgt, 2304, eps, lane_group=lg).gref == lg
+        want = dses.register(src, tgt, rot, eps, records=True, lane_group=lg)
+        assert got.records.tobytes() == want.records.tobytes()
+    compare_records(got.records[:5], oracle.records(src, tgt, rot[:5], eps), n, label=f"{n}x{m}")
+
+
 def _problems():
     """Problems of both paths, the general ones with 16- and 32-bit counters and unsorted."""
     out = []
     for i, (n, m, eps, clustered) in enumerate([
             (60, 300, 0.05, 0), (100, 350, 0.01, 0), (140, 400, 0.03, 0), (180, 450, 0.0125, 420),
-            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 420)]):
+            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 0)]):
         src, tgt, rot = clouds(n, m, 40 + i, clustered)
-        r = route(n, tgt, len(rot), eps)
+        r = route(n, tgt, len(rot), eps, batched=True)
         assert (r.gref == 0) == (i in (1, 3, 4, 5)) and r.bits == (32 if clustered else r.bits)
         out.append(dict(src=src, tgt=tgt, rotations=rot, eps=eps))
     return out
@@ -100,7 +120,7 @@ def test_server_mixes_both_paths():
     for i in range(12):
         n, eps = 70 + 45 * i, (0.01, 0.03, 0.0125)[i % 3]
         src = clouds(n, 900, 5)[0]
-        assert (route(n, tgt, len(rot), eps).gref == 0) == (i % 3 == 0)
+        assert (route(n, tgt, len(rot), eps, batched=True).gref == 0) == (i % 3 == 0)
         reqs.append((src, eps))
     with_records = [i % 2 == 0 for i in range(12)]
     want = [dses.register(src, tgt, rot, eps, records=True) for src, eps in reqs]

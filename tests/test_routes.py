@@ -16,6 +16,29 @@ def test_group_of_wide_planes(n, m, group):
         assert route(n, tgt, 1000, 0.01, lane_group=asked).group == asked
 
 
+# (lane group, parts of its windows) of the windowed vote; 0 and the general path's group
+# where that is faster; the same in a batch, whose 32-bit kernels hold groups of 64 only and
+# whose general path is for problems that cannot take the other
+@pytest.mark.parametrize("n,m,eps,clustered,plain,batched", [
+    (717, 1024, 0.03, 0, (32, 2, 0), (32, 2, 0)),           # windows of 110 sources
+    (2000, 8192, 0.03, 0, (64, 1, 0), (64, 1, 0)),
+    (5298, 853, 0.0461, 0, (32, 2, 0), (64, 4, 0)),
+    (400, 1000, 0.0118, 0, (32, 1, 0), (32, 1, 0)),         # of 8: not split
+    (100, 3000, 0.0118, 0, (64, 1, 0), (64, 1, 0)),         # of 1: few units
+    (200, 17555, 0.0118, 0, (0, 0, 64), (64, 1, 0)),
+    (12000, 100, 0.0118, 0, (0, 0, 16), (32, 8, 0)),        # 32 points span 39 bins
+    (4000, 1000, 0.0118, 0, (0, 0, 16), (32, 2, 0)),
+    (5298, 853, 0.0461, 285, (0, 0, 16), (64, 4, 0)),       # a third in one cell
+])
+def test_layout(n, m, eps, clustered, plain, batched):
+    _, tgt, _ = clouds(n, m, 1, clustered)
+    for want, b in ((plain, False), (batched, True)):
+        r = route(n, tgt, 2304, eps, batched=b)
+        assert (r.gref, r.windows, r.group) == want
+    for asked, gref in ((16, 32), (32, 32), (64, 64)):
+        assert route(n, tgt, 2304, eps, lane_group=asked).gref == gref
+
+
 # slabs of few rotations: parts taken at 1, 100, 257, 576 and 2,304 rotations
 @pytest.mark.parametrize("n,m,eps,parts", [
     (500, 3000, 0.04, (2, 2, 1, 1, 1)), (500, 3000, 0.035, (3, 2, 3, 1, 1)),
