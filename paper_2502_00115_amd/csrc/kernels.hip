@@ -428,7 +428,12 @@ __device__ __forceinline__ T kload(const T *p)
 
 // The sweep's arguments for one phase of a rotation (sort, vote, scan, score), read
 // again where the phase begins: kept over a whole rotation, the arguments of every
-// phase together take more scalar registers than there are.
+// phase together take more scalar registers than there are.  Within the vote they are
+// read once for all slabs in the general path and under 16-bit counters, whose slabs may
+// be many and short (us a rotation, read again for each slab / once: 55 x 4 points, 211
+// slabs 2.32 / 2.18; 717 x 1,024 at a pitch of 0.01 2.69 / 2.59; 100 x 3,000 at 0.0118 1.84 /
+// 1.80; 717 x 1,024 at 0.03 0.297 / 0.296), and for each slab under 32-bit ones (4,096 x
+// 16,384 points 14.49 / 14.54).
 __device__ __forceinline__ SweepArgs phase_args(const SweepArgs *p)
 {
     asm volatile("" : "+s"(p));
@@ -844,10 +849,9 @@ __device__ __forceinline__ void src_window(const SweepArgs &a, __amdgpu_buffer_r
 //   0:      lanes hold 64 rotated sources, the stream is the whole reference.
 // GROUP is a constant because as a run-time value it cost 1.5% of the sweep.
 template <int CW, int GROUP, bool WIDE>
-__device__ __forceinline__ void vote_slab(const SweepArgs *args, int32_t *sp, int k, int x0,
+__device__ __forceinline__ void vote_slab(const SweepArgs &a, int32_t *sp, int k, int x0,
                                           int np, uint32_t *hist)
 {
-    const SweepArgs a = phase_args(args);
     const Geom &g = a.g;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t Sy = g.size[1], Sz = g.size[2];
@@ -1064,11 +1068,11 @@ __device__ __forceinline__ Windows group_windows(const SweepArgs &a, __amdgpu_bu
 // group, when it first needs one of them, so that a unit starts with one memory
 // round trip (its reference points beside its first sources).
 template <int CW, int GREF>
-__device__ __forceinline__ void vote_windows(const SweepArgs *args, int32_t *sp, int x0, int np,
-                                             uint32_t *hist)
+__device__ __forceinline__ void vote_windows(const SweepArgs *args, const SweepArgs &held,
+                                             int32_t *sp, int x0, int np, uint32_t *hist)
 {
     using S = Shape<GREF>;
-    const SweepArgs a = phase_args(args);
+    const SweepArgs a = CW == 16 ? held : phase_args(args);
     const Geom &g = a.g;
     const int lane = threadIdx.x & 63;
     const uint32_t Sy = g.size[1], Sz = g.size[2];
@@ -1631,21 +1635,21 @@ __device__ __forceinline__ void score_candidate(const SweepArgs *args, int k, in
 }
 
 // The vote of one slab in the general path: planes too wide for the windowed
-// vote's 16-bit strides, or sources too many to be sorted.
+// vote's 16-bit strides, sources too many to be sorted, or where it is the faster.
 template <int CW>
-__device__ __forceinline__ void vote_slab_any(const SweepArgs *args, int32_t *sp, int k, int x0,
+__device__ __forceinline__ void vote_slab_any(const SweepArgs &a, int32_t *sp, int k, int x0,
                                               int np, uint32_t *hist, bool wide, int group)
 {
     if (!sp && !wide)
-        vote_slab<CW, 0, false>(args, sp, k, x0, np, hist);
+        vote_slab<CW, 0, false>(a, sp, k, x0, np, hist);
     else if (!sp)
-        vote_slab<CW, 0, true>(args, sp, k, x0, np, hist);
+        vote_slab<CW, 0, true>(a, sp, k, x0, np, hist);
     else if (group == 16)
-        vote_slab<CW, 16, true>(args, sp, k, x0, np, hist);
+        vote_slab<CW, 16, true>(a, sp, k, x0, np, hist);
     else if (group == 32)
-        vote_slab<CW, 32, true>(args, sp, k, x0, np, hist);
+        vote_slab<CW, 32, true>(a, sp, k, x0, np, hist);
     else
-        vote_slab<CW, 64, true>(args, sp, k, x0, np, hist);
+        vote_slab<CW, 64, true>(a, sp, k, x0, np, hist);
 }
 
 // Vote, mode and score one rotation k with the whole workgroup; sp is the
@@ -1680,9 +1684,9 @@ __device__ __forceinline__ void vote_mode(const SweepArgs *args, int k, uint32_t
     for (int x0 = PART ? first * pps : 0; x0 < size_x; x0 += PART ? step * pps : pps) {
         const int np = min(pps, size_x - x0);
         if (GREF)
-            vote_windows<CW, GREF ? GREF : 64>(args, sp, x0, np, hist);
+            vote_windows<CW, GREF ? GREF : 64>(args, a, sp, x0, np, hist);
         else
-            vote_slab_any<CW>(args, sp, k, x0, np, hist, g.wide != 0, a.group);
+            vote_slab_any<CW>(a, sp, k, x0, np, hist, g.wide != 0, a.group);
         __syncthreads();
         SlabWords words;
         const uint32_t c = take_slab<CW>(hist, (int)((uint32_t)np * plane + 3) >> 2, words);
