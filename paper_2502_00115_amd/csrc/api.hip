@@ -280,7 +280,7 @@ int window_parts(const Geom &g, int gref, float x_extent, int asked)
 // besides the slab's planes, so larger groups stream more sources, but they are fewer
 // and need half the loads per pair; a unit's set-up is worth kUnit pairs.  64 points are
 // taken only where every wave gets a group (1,500 x 300 points 0.25 / 0.28 us).  The
-// general path pays more for a pair and a unit, but it has groups of 16 points, which
+// general path pays more for a pair, a unit and a rotation, but it has groups of 16 points, which
 // matter where even 32 span more than a slab, and whose pairs meet less often in one
 // counter where a few lattice cells hold much of the reference.  The share of the pairs
 // that lie in the box in x is that of two clouds of the reference's extent about its
@@ -291,7 +291,8 @@ int window_parts(const Geom &g, int gref, float x_extent, int asked)
 VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t population, int asked,
                          bool batched)
 {
-    constexpr double kUnit = 300.0, kLarge = 0.95, kGeneralUnit = 600.0, kGeneral = 1.1;
+    constexpr double kUnit = 300.0, kLarge = 0.95;
+    constexpr double kGeneralUnit = 600.0, kGeneral = 1.13, kGeneralRotation = 12000.0;
     VoteLayout l{0, 64, 0, 0.0};
     if (!sorted) return l;
     l.group = choose_group(g, x_extent, asked, 0);
@@ -316,7 +317,7 @@ VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t pop
     l.general = HUGE_VAL;
     if (asked) return l;
     const int groups = (g.m + 15) / 16;
-    const double general = kGeneralUnit * groups * vote_parts_auto(groups) +
+    const double general = kGeneralRotation / g.nslabs + kGeneralUnit * groups * vote_parts_auto(groups) +
                            kGeneral * pairs * (groups * 16 / m) * reach(16) * (1.0 + 2.2 * full);
     l.group = 16;
     l.general = general / cost[large];

@@ -422,10 +422,20 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
     // list); n_general is their number
     int n_general = 0;
     std::vector<VoteLayout> vote(count);
+    bool forced = false, all = true;        // of the windowed ones: all gain from the general path
     for (int i = 0; i < count; ++i)
-        if (P[i].status == DSES_OK)
+        if (P[i].status == DSES_OK) {
             vote[i] = choose_layout(P[i].g, P[i].sorted, ref_x_extent(P[i].ylo, P[i].yhi),
                                     P[i].population, 0, true);
+            forced = forced || vote[i].gref == 0;
+            all = all && (vote[i].gref == 0 || vote[i].general < kBatchGeneral);
+        }
+    // a second launch ends on its own: not for some problems' sake alone (two of 100 and
+    // 400 x 2,000 points and 200 rotations, one of them general by choice, 610 -> 780 us;
+    // one of 19,800 points among 18 of 3 to 31 reference points 9.5 ms with all of them
+    // general, 12.3 with the rest windowed)
+    for (auto &v : vote)
+        if ((forced || all) && v.gref && v.general < kBatchGeneral) v.gref = v.parts = 0;
     auto build_items = [&](int items_per_cu, std::vector<BatchItem> *list) {
         const double target_cost = std::max(1.0, total / ((double)grid * items_per_cu));
         struct Tile { bool general; double cost; BatchItem it; };

@@ -156,12 +156,15 @@ struct VoteLayout {
 };
 // population: ref_block_population; asked: the caller's lane_group.  batched: the
 // batched kernels hold groups of 32 or 64 points under 16-bit counters and of 64 under
-// 32-bit ones.  The plain path compares `general` with the share that choose_parts leaves.
+// 32-bit ones.  The caller compares `general`: the plain path with the share that
+// choose_parts leaves, the others with kBatchGeneral, because the general path takes a
+// launch or a slice of its own there.
 VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t population, int asked,
                          bool batched);
 // Parts of a lane group's windows in the windowed vote, a power of two; asked: the
 // caller's vote_parts if not 0.
 int window_parts(const Geom &g, int gref, float x_extent, int asked);
+constexpr double kBatchGeneral = 0.85;
 // Reference points per lane group of the general path's vote with sorted sources: 16,
 // 32 or 64 (`asked` if not 0); vote_parts as in SweepArgs.
 int choose_group(const Geom &g, float x_extent, int asked, int vote_parts);

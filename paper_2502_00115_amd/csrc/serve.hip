@@ -329,7 +329,8 @@ dses_status ServerImpl::prepare(Request *r)
     const TargetRes::Stage *stg = nullptr;
     int32_t ylo = 0, yhi = 0;
     const bool sorted = r->n <= kSortMax && target_x_range(tm, r->p, &ylo, &yhi);
-    const VoteLayout lay = choose_layout(g, sorted, ref_x_extent(ylo, yhi), population, 0, true);
+    VoteLayout lay = choose_layout(g, sorted, ref_x_extent(ylo, yhi), population, 0, true);
+    if (lay.general < kBatchGeneral) lay.gref = lay.parts = 0;
     if ((st = ensure_target_stage(tm, r->p, g, lay.gref, up, &stg)) != DSES_OK) return st;
     CellGrid cg{};
     if (r->scorer == DSES_SCORER_GRID && (st = ensure_target_grid(tm, r->p.r, &cg)) != DSES_OK)

@@ -1,5 +1,5 @@
-// Which layout the library picks for a plain call or a problem of a batch: its own host
-// rules, called directly.
+// Which layout the library picks for a plain call or a batch of one problem: its own
+// host rules, called directly.
 #include "host.h"
 
 #include <chrono>
@@ -27,7 +27,7 @@ extern "C" int route(const float *tgt, int m, int n, int k, float eps, float box
     VoteLayout l = choose_layout(g, sorted, x, population, lane_group, batched);
     double share = 1.0;
     int parts = l.gref && !batched ? choose_parts(g, k, x, 256, &share) : 1;
-    if (!batched && l.general < share) {
+    if (l.general < (batched ? kBatchGeneral : share)) {
         l.gref = l.parts = 0;
         parts = 1;
     }

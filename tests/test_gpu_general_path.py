@@ -79,10 +79,10 @@ def _problems():
     out = []
     for i, (n, m, eps, clustered) in enumerate([
             (60, 300, 0.05, 0), (100, 350, 0.01, 0), (140, 400, 0.03, 0), (180, 450, 0.0125, 420),
-            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 0)]):
+            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 0), (6000, 100, 0.0118, 0)]):
         src, tgt, rot = clouds(n, m, 40 + i, clustered)
         r = route(n, tgt, len(rot), eps, batched=True)
-        assert (r.gref == 0) == (i in (1, 3, 4, 5)) and r.bits == (32 if clustered else r.bits)
+        assert (r.gref == 0) == (i in (1, 3, 4, 5, 7)) and r.bits == (32 if clustered else r.bits)
         out.append(dict(src=src, tgt=tgt, rotations=rot, eps=eps))
     return out
 
@@ -96,13 +96,17 @@ def test_batch_mixes_both_paths():
     replays, with windowed-only and general-only batches in between; any split of the windows."""
     probs = _problems()
     alone = [_alone(p).records.tobytes() for p in probs]
-    general = [1, 3, 4, 5]
+    general = [1, 3, 4, 5, 7]
     windowed = [0, 2, 6]
     every = list(range(len(probs)))
     for which, graph in ((every, True), (every, False), (every, True), (windowed, True),
                          (general, True), (every, True), (general, False)):
         got, st = dses.register_batch([probs[i] for i in which], records=True, use_graph=graph)
         assert st == [0] * len(which)
+        assert [g.records.tobytes() for g in got] == [alone[i] for i in which]
+    # problems that would gain: all of them together, or not for their own sake
+    for which in ([7, 7], [7, 0], [0, 7, 6]):
+        got, _ = dses.register_batch([probs[i] for i in which], records=True)
         assert [g.records.tobytes() for g in got] == [alone[i] for i in which]
     for parts in (1, 3, 16):
         got, _ = dses.register_batch(probs, records=True, vote_parts=parts)

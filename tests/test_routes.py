@@ -18,7 +18,7 @@ def test_group_of_wide_planes(n, m, group):
 
 # (lane group, parts of its windows) of the windowed vote; 0 and the general path's group
 # where that is faster; the same in a batch, whose 32-bit kernels hold groups of 64 only and
-# whose general path is for problems that cannot take the other
+# where the general path has to gain clearly
 @pytest.mark.parametrize("n,m,eps,clustered,plain,batched", [
     (717, 1024, 0.03, 0, (32, 2, 0), (32, 2, 0)),           # windows of 110 sources
     (2000, 8192, 0.03, 0, (64, 1, 0), (64, 1, 0)),
@@ -26,9 +26,9 @@ def test_group_of_wide_planes(n, m, group):
     (400, 1000, 0.0118, 0, (32, 1, 0), (32, 1, 0)),         # of 8: not split
     (100, 3000, 0.0118, 0, (64, 1, 0), (64, 1, 0)),         # of 1: few units
     (200, 17555, 0.0118, 0, (0, 0, 64), (64, 1, 0)),
-    (12000, 100, 0.0118, 0, (0, 0, 16), (32, 8, 0)),        # 32 points span 39 bins
+    (12000, 100, 0.0118, 0, (0, 0, 16), (0, 0, 16)),        # 32 points span 39 bins
     (4000, 1000, 0.0118, 0, (0, 0, 16), (32, 2, 0)),
-    (5298, 853, 0.0461, 285, (0, 0, 16), (64, 4, 0)),       # a third in one cell
+    (5298, 853, 0.0461, 285, (0, 0, 16), (0, 0, 16)),       # a third in one cell
 ])
 def test_layout(n, m, eps, clustered, plain, batched):
     _, tgt, _ = clouds(n, m, 1, clustered)
