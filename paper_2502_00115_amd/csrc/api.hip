@@ -255,14 +255,15 @@ dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, i
 }
 
 // Parts of a lane group's windows in the windowed vote, a power of two: `asked` rounded
-// down, or about kVoteUnits units per slab for the 16 waves, at most 8, with no part
-// shorter than a block of 16 sources on average but for two units a wave.  Halving the
+// down, or at most 96 units per slab for the 16 waves (128 of at least 128 sources on
+// average, because 49 to 64 units leave a part of the waves without a last one: 5,520 x
+// 1,540 points at 0.03 2.27 / 2.09 us a rotation, 5,520 x 3,103 at 0.052 3.48 / 3.21) and at
+// most 8, with no part shorter than a block of 16 but for two units a wave.  Halving the
 // parts of shorter ones took 0.78 to 0.93 of the time (100 x 3,000 points at 0.0118 2.37 /
 // 1.86 us a rotation, 400 x 1,000 2.13 / 1.88), of parts of 20 to 300 sources 1.0 to 1.18
 // (1,500 x 2,000 at 0.015 4.07 / 4.36, 4,000 x 1,000 2.41 / 2.74).
 int window_parts(const Geom &g, int gref, float x_extent, int asked)
 {
-    constexpr int kVoteUnits = 96;
     int parts = 1;
     if (asked > 0) {
         while (parts < 16 && 2 * parts <= asked) parts *= 2;
@@ -270,9 +271,12 @@ int window_parts(const Geom &g, int gref, float x_extent, int asked)
     }
     const int groups = (g.m + gref - 1) / gref;
     const double window = (g.pps + (double)gref * x_extent / g.m) * g.n / (x_extent + g.size[0]);
-    while (parts < 8 && groups * 2 * parts <= kVoteUnits &&
-           (window >= 2 * parts * 16 || groups * 2 * parts <= 32))
+    while (parts < 8) {
+        const int units = groups * 2 * parts;
+        const double part = window / (2 * parts);
+        if (units > 128 || part < (units > 96 ? 128 : (units > 32 ? 16 : 0))) break;
         parts *= 2;
+    }
     return parts;
 }
 

@@ -22,7 +22,7 @@ def test_group_of_wide_planes(n, m, group):
 @pytest.mark.parametrize("n,m,eps,clustered,plain,batched", [
     (717, 1024, 0.03, 0, (32, 2, 0), (32, 2, 0)),           # windows of 110 sources
     (2000, 8192, 0.03, 0, (64, 1, 0), (64, 1, 0)),
-    (5298, 853, 0.0461, 0, (32, 2, 0), (64, 4, 0)),
+    (5298, 853, 0.0461, 0, (32, 4, 0), (64, 8, 0)),        # of 400: up to 128 units
     (400, 1000, 0.0118, 0, (32, 1, 0), (32, 1, 0)),         # of 8: not split
     (100, 3000, 0.0118, 0, (64, 1, 0), (64, 1, 0)),         # of 1: few units
     (200, 17555, 0.0118, 0, (0, 0, 64), (64, 1, 0)),
