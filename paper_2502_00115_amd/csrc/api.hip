@@ -312,7 +312,8 @@ VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t pop
     for (int i = 0; i < 2; ++i) {
         const int gref = 32 << i, groups = (g.m + gref - 1) / gref;
         cost[i] = kUnit * groups * window_parts(g, gref, x_extent, 0) +
-                  pairs * (groups * gref / m) * reach(gref) * (i ? kLarge : 1.0) * (1.0 + 5.0 * full);
+                  (i ? kLarge : 1.0) * pairs * (groups * gref / m) * reach(gref) *
+                      (1.0 + 5.0 * full);
     }
     const bool large = asked ? asked > 32 : (batched && g.counter_bits == 32) ||
                                               (g.m > 15 * 64 && cost[1] < cost[0]);
@@ -321,7 +322,8 @@ VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t pop
     l.general = HUGE_VAL;
     if (asked) return l;
     const int groups = (g.m + 15) / 16;
-    const double general = kGeneralRotation / g.nslabs + kGeneralUnit * groups * vote_parts_auto(groups) +
+    const double general = kGeneralRotation / g.nslabs +
+                           kGeneralUnit * groups * vote_parts_auto(groups) +
                            kGeneral * pairs * (groups * 16 / m) * reach(16) * (1.0 + 2.2 * full);
     l.group = 16;
     l.general = general / cost[large];

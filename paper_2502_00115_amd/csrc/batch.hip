@@ -418,11 +418,10 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
             sum_k += x.k;
             ++n_ok;
         }
-    // (the general path's tiles, which a launch of their own runs, at the end of the
-    // list); n_general is their number
+    // n_general: the general path's tiles, at the end of the list
     int n_general = 0;
     std::vector<VoteLayout> vote(count);
-    bool forced = false, all = true;        // of the windowed ones: all gain from the general path
+    bool forced = false, all = true;        // some need the general path; the rest gain by it
     for (int i = 0; i < count; ++i)
         if (P[i].status == DSES_OK) {
             vote[i] = choose_layout(P[i].g, P[i].sorted, ref_x_extent(P[i].ylo, P[i].yhi),
@@ -430,10 +429,10 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
             forced = forced || vote[i].gref == 0;
             all = all && (vote[i].gref == 0 || vote[i].general < kBatchGeneral);
         }
-    // a second launch ends on its own: not for some problems' sake alone (two of 100 and
-    // 400 x 2,000 points and 200 rotations, one of them general by choice, 610 -> 780 us;
-    // one of 19,800 points among 18 of 3 to 31 reference points 9.5 ms with all of them
-    // general, 12.3 with the rest windowed)
+    // a second launch ends on its own, so no problem asks for one by choice alone (two of
+    // 200 and 400 x 2,000 points and 200 rotations, one of them general by choice, 610 ->
+    // 780 us); where all gain or one is there anyway they join it (18 of up to 19,800 x 31
+    // points 15.7 -> 12.8 ms)
     for (auto &v : vote)
         if ((forced || all) && v.gref && v.general < kBatchGeneral) v.gref = v.parts = 0;
     auto build_items = [&](int items_per_cu, std::vector<BatchItem> *list) {
@@ -576,8 +575,9 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                 a.field.inv[q] = x.target->df_inv[q];
             }
         }
-        sd = stage_desc(x.g, a.gref,
-                        worth_arranging(x.g, a.gref, ref_x_extent(x.ylo, x.yhi), x.k), x.tgt, perm_dev, const_cast<int32_t *>(a.yq), const_cast<float *>(a.yt));
+        const bool arrange = worth_arranging(x.g, a.gref, ref_x_extent(x.ylo, x.yhi), x.k);
+        sd = stage_desc(x.g, a.gref, arrange, x.tgt, perm_dev, const_cast<int32_t *>(a.yq),
+                        const_cast<float *>(a.yt));
         sl = SelectDesc{a.rec, x.k, x.p.delta, x.rot, res_dev + i, status_dev + i};
     }
     int32_t header[3] = {n_items - n_general, count, n_items};

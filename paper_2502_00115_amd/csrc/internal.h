@@ -105,9 +105,9 @@ struct SweepArgs {
 };
 
 // Scratch slot of one workgroup (int32 words): rotated fixed-point sources sorted
-// by x as three arrays x, y, z of src_stride(cap) entries each (entries n ..
-// stride-1 hold padding that never votes, so windows can be padded to a multiple
-// of 4), then the bucket table T[0 .. kSrcBuckets] (T[b] = sources in buckets
+// by x as an array of x and one of 64-bit -(y, z) words, of src_stride(cap) entries
+// each (entries n .. stride-1 hold padding that never votes, so windows can be padded
+// to a multiple of 4), then the bucket table T[0 .. kSrcBuckets] (T[b] = sources in buckets
 // below b).
 __host__ __device__ inline int64_t src_stride(int64_t cap) { return (cap + 15) & ~int64_t(15); }
 __host__ __device__ inline int64_t slot_words(int64_t cap)

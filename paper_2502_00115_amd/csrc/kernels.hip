@@ -8,9 +8,9 @@
 //    (y, z) array and a bucket table).
 //  * In the vote each lane holds two or four points of the x-sorted reference (a work
 //    unit's lane group of 32 or 64 consecutive points on 16 lanes, repeated on the
-//    wave's four lane sub-groups) and streams the sources of the window whose pairs
-//    can land in the current slab; the sub-groups take alternate 4-source pieces of
-//    it.  Sources arrive through 16-byte buffer loads (one address per sub-group), two
+//    wave's four lane sub-groups; in the general path 16, 32 or 64 points, two a lane)
+//    and streams the sources of the window whose pairs can land in the current slab;
+//    the sub-groups take alternate 4-source pieces of it.  Sources arrive through 16-byte buffer loads (one address per sub-group), two
 //    blocks in flight.  A pair's bin is exact integer arithmetic: one 64-bit add for
 //    the y and z differences, one subtraction for x, the bin being the high 16 bits
 //    of each.
@@ -516,7 +516,7 @@ struct VoteConst {
     asm volatile("s_mov_b64 %[save], exec\n\t" TEXT "ds_add_u32 %[t1], %[t2]\n\t"            \
                  "s_mov_b64 exec, %[save]"                                                   \
                  : [save] "=&s"(save), [t1] "=&v"(t1), [t2] "=&v"(t2)                          \
-                 : DSES_VP_OPERANDS, [half] "v"(v.half), [k16] "v"(v.k16)                                     \
+                 : DSES_VP_OPERANDS, [half] "v"(v.half), [k16] "v"(v.k16)                      \
                  : "vcc", "memory")
 #define DSES_VP_ASM32(TEXT)                                                                  \
     asm volatile("s_mov_b64 %[save], exec\n\t" TEXT "ds_add_u32 %[t1], %[t2]\n\t"            \
@@ -576,13 +576,13 @@ __device__ __forceinline__ f4u desc_words(const void *base, int64_t bytes)
 }
 
 // Byte offsets of the x, y and z arrays of a point set held as int32 arrays of
-// `stride` entries (z is array zsel: 2, or 3 for the reference's 2^-15 z).
+// `stride` entries.
 struct SoaOffs {
     int o0, o1, o2;
 };
-__device__ __forceinline__ SoaOffs soa_offs(int stride, int zsel)
+__device__ __forceinline__ SoaOffs soa_offs(int stride)
 {
-    return SoaOffs{0, 4 * stride, 4 * zsel * stride};
+    return SoaOffs{0, 4 * stride, 8 * stride};
 }
 
 // Points j .. j+3 (x, y, z) of such a set: three 16-byte loads, the same address
@@ -750,8 +750,7 @@ __device__ __forceinline__ void vote8(f4u x, f4u yz01, f4u yz23, const LanePts &
 // j1 - j0 a multiple of 4: in each whole block of B = 4 * 64 / (lanes per copy of
 // the group) points, lane sub-group h (its hoff = 16 h bytes) takes points
 // 4h .. 4h + 3; the r < B points after the last whole block go in r / S steps
-// (S = B / 4 sub-groups), sub-group h taking point S q + h in step q (every index
-// stays below j1).  A whole block inside [i0, i1) (the window's interior) is voted
+// (S = B / 4 sub-groups), sub-group h taking point S q + h in step q.  A whole block inside [i0, i1) (the window's interior) is voted
 // without the x test; the choice is a uniform branch per block, so the loads stay
 // one pipeline, two blocks in flight, across the whole range.
 template <int CW, bool WIDE>
@@ -760,7 +759,7 @@ __device__ __forceinline__ void vote_span_lanes(const f4u &desc, __amdgpu_buffer
                                                 uint32_t hoff, const LanePts &L,
                                                 const VoteConst &v)
 {
-    const int jb = B > 4 ? j0 + (j1 - j0) / B * B : j1;   // B == 4: no tail
+    const int jb = j0 + (j1 - j0) / B * B;
     const uint32_t hoff2 = 2u * hoff;
     for (int t = jb; t < j1; t += B >> 2) {
         // with 8 sub-groups the last step may reach 4 points past j1: those lanes
@@ -945,7 +944,7 @@ __device__ __forceinline__ void vote_slab(const SweepArgs &a, int32_t *sp, int k
         const int total = nsg * G;
         const f4u rdesc = desc_words(a.yq, 12 * (int64_t)m);
         const __amdgpu_buffer_rsrc_t rrs = rsrc(a.yq, 12 * (int64_t)m);
-        const SoaOffs so = soa_offs(m, 2);
+        const SoaOffs so = soa_offs(m);
         const double Sz = CW == 16 ? g.S15 : g.S16;
         float R[9];
         load_rotation(a, k, R);
@@ -1652,10 +1651,10 @@ __device__ __forceinline__ void vote_slab_any(const SweepArgs &a, int32_t *sp, i
         vote_slab<CW, 64, true>(a, sp, k, x0, np, hist);
 }
 
-// Vote, mode and score one rotation k with the whole workgroup; sp is the
-// workgroup's source-sort scratch (null: sources not sorted).  Writes a.rec[k].
-// Slabs first, first + step, ... of rotation k (all of them unless PART): the largest
-// count and the lowest position that holds it, for every thread.
+// Vote and mode of one rotation k with the whole workgroup, over its slabs first,
+// first + step, ... (all of them unless PART): the largest count and the lowest position
+// that holds it, for every thread.  sp is the workgroup's source-sort scratch (null:
+// sources not sorted).
 template <int CW, int GREF, bool PART>
 __device__ __forceinline__ void vote_mode(const SweepArgs *args, int k, uint32_t *lds, int32_t *sp,
                                           int first, int step, uint32_t &best_c, uint32_t &best_p)
@@ -1700,7 +1699,8 @@ __device__ __forceinline__ void vote_mode(const SweepArgs *args, int k, uint32_t
         if (m > best_c) {
             best_c = m;
             wave_p = 0xFFFFFFFFu;
-            if (c == m) wave_p = (uint32_t)x0 * plane * (CW == 16 ? 2u : 1u) + first_of<CW>(words, m);
+            if (c == m)
+                wave_p = (uint32_t)x0 * plane * (CW == 16 ? 2u : 1u) + first_of<CW>(words, m);
         }
     }
     if ((tid & 63) == 0) scr[24 + (tid >> 6)] = wave_p;
@@ -1738,6 +1738,7 @@ __device__ __forceinline__ void score_mode(const SweepArgs *args, int k, uint32_
     score_candidate<SCORER>(args, k, bx, by, bz, best_c, lds);
 }
 
+// Vote, mode and score of one rotation k; writes a.rec[k].
 template <int CW, int SCORER, int GREF>
 __device__ __forceinline__ void sweep_one(const SweepArgs *args, int k, uint32_t *lds, int32_t *sp)
 {
@@ -2550,9 +2551,9 @@ __device__ __forceinline__ void sweep_item(const SweepArgs *args, const BatchIte
     for (int k = w.k0; k < w.k1; ++k) sweep_one<CW, SCORER, GREF>(args, k, lds, sp);
 }
 
-// GENERAL: the items of instances that only the general path can run, header[0] ..
-// header[2] of the list, taken by a launch of their own (so that the windowed
-// vote's kernel holds no other code); else items 0 .. header[0].
+// GENERAL: the items of instances that take the general path, header[0] .. header[2] of
+// the list, by a launch of their own (so that the windowed vote's kernel holds no other
+// code); else items 0 .. header[0].
 template <int SCORER, bool GENERAL>
 __global__ void __launch_bounds__(kBlock) k_sweep_batch(BatchArgs b)
 {
@@ -2625,7 +2626,8 @@ __global__ void k_stage_batch(const StageDesc *d, const int32_t *header)
     }
 }
 
-__global__ void __launch_bounds__(kArrangeBlock) k_arrange_batch(const StageDesc *d, const int32_t *header)
+__global__ void __launch_bounds__(kArrangeBlock) k_arrange_batch(const StageDesc *d,
+                                                                 const int32_t *header)
 {
     __shared__ float P[64 * 65];
     __shared__ uint32_t mask[64];
@@ -2688,7 +2690,8 @@ hipError_t launch_batch_aux(const StageDesc *stage, const SelectDesc *sel, const
     const int gy = max_count < 1 ? 1 : (max_count > 65535 ? 65535 : max_count);
     if (which == 0) {
         hipLaunchKernelGGL(k_stage_batch, dim3(16, gy), dim3(256), 0, stream, stage, header);
-        hipLaunchKernelGGL(k_arrange_batch, dim3(64, gy), dim3(kArrangeBlock), 0, stream, stage, header);
+        hipLaunchKernelGGL(k_arrange_batch, dim3(64, gy), dim3(kArrangeBlock), 0, stream, stage,
+                           header);
     } else
         hipLaunchKernelGGL(k_select_batch, dim3(gy), dim3(64), 0, stream, sel, header);
     return hipGetLastError();

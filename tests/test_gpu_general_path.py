@@ -79,7 +79,8 @@ def _problems():
     out = []
     for i, (n, m, eps, clustered) in enumerate([
             (60, 300, 0.05, 0), (100, 350, 0.01, 0), (140, 400, 0.03, 0), (180, 450, 0.0125, 420),
-            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 0), (6000, 100, 0.0118, 0)]):
+            (16385, 5, 0.05, 0), (717, 1024, 0.01, 0), (200, 500, 0.05, 0),
+            (6000, 100, 0.0118, 0)]):
         src, tgt, rot = clouds(n, m, 40 + i, clustered)
         r = route(n, tgt, len(rot), eps, batched=True)
         assert (r.gref == 0) == (i in (1, 3, 4, 5, 7)) and r.bits == (32 if clustered else r.bits)
