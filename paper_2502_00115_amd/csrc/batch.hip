@@ -65,7 +65,6 @@ struct GraphCache {
     int scorer = -1;
     int cap_count = 0, cap_items = 0, grid = 0;
     hipStream_t stream = nullptr;
-    bool general = false;
 };
 
 struct BatchState {
@@ -73,7 +72,7 @@ struct BatchState {
     DevResult *host_res = nullptr;
     int cap_count = 0, cap_items = 0;
     size_t cap_scratch = 0;
-    GraphCache graph[4];
+    GraphCache graph[4][2];            // by scorer, without and with the general path's launch
 };
 
 BatchState *g_batch = nullptr;
@@ -141,10 +140,11 @@ static dses_status ensure_capacity(BatchState *b, int count, int n_items, size_t
         grew = true;
     }
     if (grew)
-        for (auto &gc : b->graph) {
-            if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
-            gc.exec = nullptr;
-        }
+        for (auto &kinds : b->graph)
+            for (auto &gc : kinds) {
+                if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
+                gc.exec = nullptr;
+            }
     return DSES_OK;
 }
 
@@ -174,9 +174,9 @@ static dses_status enqueue_batch(BatchState *b, int scorer, bool general, int gr
 
 static dses_status run_graph(BatchState *b, int scorer, bool general, int grid, hipStream_t stream)
 {
-    GraphCache &gc = b->graph[scorer];
+    GraphCache &gc = b->graph[scorer][general];
     if (!gc.exec || gc.cap_count != b->cap_count || gc.cap_items != b->cap_items ||
-        gc.grid != grid || gc.stream != stream || gc.general != general) {
+        gc.grid != grid || gc.stream != stream) {
         if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
         gc.exec = nullptr;
         hipGraph_t graph = nullptr;
@@ -196,7 +196,6 @@ static dses_status run_graph(BatchState *b, int scorer, bool general, int grid, 
         gc.cap_items = b->cap_items;
         gc.grid = grid;
         gc.stream = stream;
-        gc.general = general;
     }
     DSES_HIP(hipGraphLaunch(gc.exec, stream));
     return DSES_OK;
