@@ -896,6 +896,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     if (parts > 1 &&
         (st = c->modes.ensure((size_t)job.k * parts * 2 * sizeof(uint32_t))) != DSES_OK)
         return st;
+    if (o.q > 0.0f && (st = c->prune.ensure(64)) != DSES_OK) return st;
     if ((st = dbuf(c->yq, stage_words(m) * sizeof(int32_t), &d_yq)) != DSES_OK) return st;
     if ((st = dbuf(c->yt, 3 * m * sizeof(float), &d_yt)) != DSES_OK) return st;
     // with an arena the records go straight to the caller's buffer when it gives one
@@ -937,6 +938,10 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         for (int q = 0; q < 3; ++q) { a.field.lo[q] = t->df_lo[q]; a.field.inv[q] = t->df_inv[q]; }
     }
 
+    const bool timing = c->timing_enabled;     // never with an arena
+    hipEvent_t ev[4] = {};
+    auto rec_ev = [&](int i) { if (timing) (void)hipEventRecord(ev[i], stream); };
+
     // What the host prepared, on the device: the status words (zero), the order by x and
     // the cell grid.  Small calls are bound by launches, copies and waits, so without an
     // arena these are one block and one asynchronous copy from pinned memory, which the
@@ -968,6 +973,11 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
                      o_start = o_pts + up(pb), total = o_start + sb;
         if ((st = c->upload.ensure(total)) != DSES_OK) return st;
         if ((st = c->host_stage.ensure(total)) != DSES_OK) return st;
+        // all that may fail on the host comes before the copy: a call that ends early would
+        // leave it in flight behind its stream's work, to overwrite the status words of a
+        // later call on another stream
+        if (timing)
+            for (auto &e : ev) DSES_HIP(hipEventCreate(&e));
         char *hs = static_cast<char *>(c->host_stage.ptr), *ds = static_cast<char *>(c->upload.ptr);
         std::memset(hs, 0, o_perm);
         std::memcpy(hs + o_perm, perm->data(), m * sizeof(int32_t));
@@ -987,12 +997,6 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
         a.grid.inv = hg.inv;
     }
 
-    const bool timing = c->timing_enabled;
-    hipEvent_t ev[4] = {};
-    if (timing)
-        for (auto &e : ev) DSES_HIP(hipEventCreate(&e));
-    auto rec_ev = [&](int i) { if (timing) (void)hipEventRecord(ev[i], stream); };
-
     prepare.end();
     TraceRange device("dses.sweep_select");    // launches to the result on the host
     rec_ev(0);
@@ -1007,7 +1011,6 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     if (job.exhaustive) {
         DSES_HIP(launch_exhaustive(a, scorer, grid, stream));
     } else if (o.q > 0.0f) {
-        if ((st = c->prune.ensure(64)) != DSES_OK) return st;
         uint32_t *pw = static_cast<uint32_t *>(c->prune.ptr);
         DSES_HIP(launch_sweep(a, kScoreNone, grid, stream));
         DSES_HIP(launch_score_pruned(a, scorer, o.q, pw, pw + 1, grid, stream));
