@@ -158,13 +158,14 @@ typedef struct {
     int32_t lane_group;       /* vote layout (sources up to 16,384 points): reference
                                  points per lane group, 32 or 64 (a wave holds four
                                  copies of the group, each streaming alternate
-                                 4-source pieces of its window; 16 is taken as 32),
-                                 or, for lattices with more than 65,535 bytes of
-                                 counters in an x plane, 16, 32 or 64 (a wave holds
-                                 128 / lane_group copies); 0 -> either vote and its
-                                 group chosen per call from the sizes and the
-                                 reference's extent and density.  Results do not
-                                 depend on it; other values are DSES_E_INVAL          */
+                                 4-source pieces of its window), or, for lattices with
+                                 more than 65,535 bytes of counters in an x plane, 16,
+                                 32 or 64 (a wave holds 128 / lane_group copies); 16
+                                 elsewhere -> 16 in that form or 32 in the other,
+                                 whichever is estimated faster; 0 -> form and group
+                                 chosen per call from the sizes and the reference's
+                                 extent and density.  Results do not depend on it;
+                                 other values are DSES_E_INVAL                        */
     int32_t df_lookup;        /* dses_df_lookup of the DF scorer; 0 -> NEAREST         */
 } dses_options;
 

@@ -320,7 +320,7 @@ VoteLayout choose_layout(const Geom &g, bool sorted, float x_extent, int64_t pop
     l.gref = large ? 64 : 32;
     l.parts = window_parts(g, l.gref, x_extent, 0);
     l.general = HUGE_VAL;
-    if (asked) return l;
+    if (asked > 16) return l;
     const int groups = (g.m + 15) / 16;
     const double general = kGeneralRotation / g.nslabs +
                            kGeneralUnit * groups * vote_parts_auto(groups) +

@@ -146,7 +146,7 @@ int counter_bits_for(int64_t bound, int32_t n, int32_t m, const Params &p);
 dses_status plan_geom(const Context *c, const Params &p, int32_t n, int32_t m, int counter_bits,
                       Geom *g);
 // How a call votes.  gref: reference points per lane group of the windowed vote (32 or
-// 64; 16 asked for is taken as 32), 0 where only the general path applies (sources not
+// 64; 16 asked for is 32, or 16 in the general path), 0 where only the general path applies (sources not
 // sorted, or x planes wider than 16-bit strides).  group: the general path's.  parts: a
 // group's windows are split into (0: vote_parts_auto of the general path).  general: the
 // general path's estimated time as a multiple of the windowed vote's.
