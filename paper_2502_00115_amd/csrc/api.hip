@@ -1000,7 +1000,7 @@ dses_status run_plain(Context *c, const Job &job, hipStream_t stream, bool check
     prepare.end();
     TraceRange device("dses.sweep_select");    // launches to the result on the host
     rec_ev(0);
-    const bool arrange = worth_arranging(g, a.gref, x_extent, job.k);
+    const bool arrange = worth_arranging(g, a.gref, x_extent, job.k, parts, c->n_cu);
     const CheckArgs ca{job.src,  job.n, job.tgt, job.m, job.rot, job.k, kSrcCoordLimit,
                        ref_coord_limit(p), bad};
     DSES_HIP(launch_prepare(check_inputs ? &ca : nullptr,

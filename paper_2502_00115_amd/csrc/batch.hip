@@ -574,7 +574,7 @@ extern "C" dses_status dses_register_batch(const dses_problem *probs, int32_t co
                 a.field.inv[q] = x.target->df_inv[q];
             }
         }
-        const bool arrange = worth_arranging(x.g, a.gref, ref_x_extent(x.ylo, x.yhi), x.k);
+        const bool arrange = worth_arranging(x.g, a.gref, ref_x_extent(x.ylo, x.yhi), x.k, 1, 1);
         sd = stage_desc(x.g, a.gref, arrange, x.tgt, perm_dev, const_cast<int32_t *>(a.yq),
                         const_cast<float *>(a.yt));
         sl = SelectDesc{a.rec, x.k, x.p.delta, x.rot, res_dev + i, status_dev + i};

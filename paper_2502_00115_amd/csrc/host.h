@@ -175,19 +175,27 @@ int choose_parts(const Geom &g, int32_t k, float x_extent, int n_cu, double *sha
 // gref points (0: the general path), in bank order if `arrange`.
 StageDesc stage_desc(const Geom &g, int gref, bool arrange, const float *tgt, const int32_t *perm,
                      int32_t *yq, float *yt);
-// Whether a call of k rotations gains from bank order (k_arrange takes 20 us for
-// groups of 32 points, 40 us for 64).  It shortens the LDS accesses of the votes that
-// land in the box, about n m k times the product of size / (2 extent) over the axes
-// for clouds of the reference's extent; 1,203 x 3,001 points and 4,608 rotations
-// (6 10^9 of them) gained 0.23 ms of 4.75.  Groups of 32 points under 16-bit counters
-// (717 x 1,024 points) issue too many other instructions to gain.
-inline bool worth_arranging(const Geom &g, int gref, float x_extent, int64_t k)
+// Whether k rotations, each split into `parts` items over n_cu workgroups, gain from bank
+// order (k_arrange takes 20 us for groups of 32 points, 40 us for 64).  It shortens the
+// LDS accesses of the votes that land in the box, about n m k times the product of
+// size / (2 extent) over the axes for clouds of the reference's extent.  A round of items
+// takes as long when it leaves workgroups idle, so k counts as whole rounds; a batch's
+// problems share their rounds (n_cu 1).  Under 32-bit counters one workgroup holds a CU and
+// waits for these accesses: from 0.4 10^9 votes every measured call gained (1,500 x 3,000
+// points and 300 rotations, 0.52: 720 to 621; 2,600 x 8,200 and 60, 0.41: 635 to 607;
+// 5,520 x 3,103 and 300, 2.0: 2,492 to 1,951) and up to 0.33 some lost (2,600 x 4,097 and
+// 60, 0.20: 375 to 404 us).  Under 16-bit ones two share a CU and hide more of them: groups of
+// 64 points still lost 3% at 1.1 (3,000 x 600 and 2,000), 1,203 x 3,001 points and 4,608
+// rotations (6.0) gained 0.23 ms of 4.75, and groups of 32 (717 x 1,024) issue too many
+// other instructions to gain.
+inline bool worth_arranging(const Geom &g, int gref, float x_extent, int64_t k, int parts, int n_cu)
 {
     if (gref == 0 || (gref == 32 && g.counter_bits == 16)) return false;
-    double votes = (double)g.n * g.m * (double)k;
+    const int64_t rounds = (k * parts + n_cu - 1) / n_cu;
+    double votes = (double)g.n * g.m * (double)(rounds * n_cu) / parts;
     for (int a = 0; a < 3; ++a)
         votes *= std::min(1.0, g.size[a] / (2.0 * (double)x_extent));
-    return votes >= 2.5e9;
+    return votes >= (g.counter_bits == 32 ? 0.4e9 : 2.5e9);
 }
 // Upper bound on any bin's vote count (decides 16- vs 32-bit LDS counters):
 // n x the largest reference population of a 2 x 2 x 2 block of cells of pitch

@@ -33,7 +33,7 @@ extern "C" int route(const float *tgt, int m, int n, int k, float eps, float box
     }
     const int32_t v[10] = {bits, g.wide, g.nslabs, g.pps, sorted, l.gref,
                            l.gref || !sorted ? 0 : l.group, l.parts,
-                           worth_arranging(g, l.gref, x, k), parts};
+                           worth_arranging(g, l.gref, x, k, parts, batched ? 1 : 256), parts};
     for (int i = 0; i < 10; ++i) out[i] = v[i];
     return DSES_OK;
 }

@@ -40,6 +40,24 @@ def test_bank_order_keeps_every_record(n, m, eps, k, lg, bits):
         assert part.records.tobytes() == got.records[lo:lo + 32].tobytes()
 
 
+# few rotations in bank order, in parts and whole, against a batch of eight, which stay in the
+# order by x
+@pytest.mark.parametrize("n,m,eps,k,lg,parts", [(5520, 3103, 0.0523, 40, 64, 2),
+                                                (5520, 3103, 0.0523, 300, 32, 2),
+                                                (3001, 3000, 0.05, 200, 64, 1),
+                                                (2600, 8200, 0.03, 100, 32, 5)])
+def test_bank_order_of_few_rotations(n, m, eps, k, lg, parts):
+    src, tgt, rot = _long(n, m, k)
+    r = route(n, tgt, k, eps, lane_group=lg)
+    assert r.arrange and r.gref == lg and r.bits == 32 and r.parts == parts
+    got = dses.register(src, tgt, rot, eps, records=True, lane_group=lg)
+    few = 8
+    assert not route(n, tgt, few, eps, lane_group=lg, batched=True).arrange
+    some, _ = dses.register_batch([dict(src=src, tgt=tgt, rotations=rot[:few], eps=eps)],
+                                  records=True)
+    assert some[0].records.tobytes() == got.records[:few].tobytes()
+
+
 def test_bank_order_in_batches_and_served():
     """The batched staging orders the groups of its long problems only; a served reference is
     always in bank order."""

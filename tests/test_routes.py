@@ -52,6 +52,20 @@ def test_parts(n, m, eps, parts):
     assert tuple(route(n, tgt, k, eps).parts for k in (1, 100, 257, 576, 2304)) == parts
 
 
+# 32-bit counters gain from bank order from few rotations on, which count as whole rounds of
+# the card's 256 workgroups; a batch's problems share theirs
+@pytest.mark.parametrize("n,m,eps,k,plain,batched", [
+    (5520, 3103, 0.0523, 300, 1, 1), (5520, 3103, 0.0523, 16, 1, 0), (1500, 3000, 0.05, 300, 1, 1),
+    (2600, 8200, 0.03, 100, 1, 1), (2600, 4097, 0.03, 60, 0, 0), (1000, 2500, 0.05, 100, 0, 0),
+    (1100, 2500, 0.03, 1000, 0, 0), (3000, 600, 0.03, 2000, 0, 0), (1100, 2500, 0.03, 4608, 1, 1),
+])
+def test_bank_order(n, m, eps, k, plain, batched):
+    _, tgt, _ = clouds(n, m, 1)
+    for lg in (64,) if n == 1100 or n == 3000 else (0, 64):
+        assert route(n, tgt, k, eps, lane_group=lg).arrange == plain
+        assert route(n, tgt, k, eps, lane_group=lg, batched=True).arrange == batched
+
+
 def test_choosing_parts_is_short():
     """Every call of up to 2,048 rotations over several slabs pays for the choice before its
     first launch: less than half of what it pays to order 8,192 points (once as much)."""
